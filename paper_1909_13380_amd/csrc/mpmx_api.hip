@@ -32,6 +32,7 @@ using namespace mpmx;
 namespace {
 
 constexpr int kParticleBlock = 256;
+static_assert(kLoadThreads == kParticleBlock, "particle_grid() sizes the load kernel's grid too");
 
 struct ProfEvent {
     const char *name;
@@ -1379,7 +1380,7 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
         const KernelSet &K = kernel_set(s->prec, s->shape);
         SceneDev *d = s->d;
         void *args[] = {&d, &dx, &dv, &dsig, &dvol, &dmass};
-        if (hipLaunchKernel(K.load, particle_grid(np), dim3(kParticleBlock), args, 0, ctx->aux) != hipSuccess)
+        if (hipLaunchKernel(K.load, particle_grid(np), dim3(kLoadThreads), args, 0, ctx->aux) != hipSuccess)
             ok = false;
     }
     if (ok && hipStreamSynchronize(ctx->aux) != hipSuccess)
@@ -1604,8 +1605,8 @@ int mpmx_scene_read(mpmx_ctx *ctx, uint64_t scene, const mpmx_particles_out *out
         const KernelSet &K = kernel_set(s->prec, s->shape);
         SceneDev *d = s->d;
         void *args[] = {&d, &dx, &dv, &ds, &dvo, &dc};
-        if (ok && hipLaunchKernel(K.read_out, particle_grid(np), dim3(kParticleBlock), args, 0, ctx->aux) !=
-                      hipSuccess)
+        const dim3 rg((unsigned)std::min<int64_t>(ceil_div(np, kReadParticles), 1 << 20));
+        if (ok && hipLaunchKernel(K.read_out, rg, dim3(kReadThreads), args, 0, ctx->aux) != hipSuccess)
             ok = false;
         if (ok && hipStreamSynchronize(ctx->aux) != hipSuccess)
             ok = false;

@@ -28,6 +28,9 @@ constexpr int kChunk = 512;               // max particles per work item
 constexpr int kXcds = 8;                  // accelerator dies (one L2 each) of the GPU
 constexpr int kBlock = 1024;              // threads per workgroup of the reorder and control kernel
 constexpr int kSortU = 4;                 // particles per lane in flight in the reorder's particle phases
+constexpr int kLoadThreads = 256;         // threads per workgroup of the particle load
+constexpr int kReadThreads = 256;         // threads per workgroup of the particle read
+constexpr int kReadParticles = 512;       // particles per workgroup pass of the particle read
 constexpr int kReorderPerCu = 1;          // most reorder workgroups per compute unit
 constexpr uint32_t kScanChunks = 4096;     // most chunks of the reorder's brick scan
 // Linear shape functions: per-thread register cache of the gathered support

@@ -56,3 +56,35 @@ def test_gimp_supports_at_their_joins(ctx, mp, algo, prec):
     s.step(4)
     check(f"gimp-joins/{algo}/{prec}", s.read(), oracle.run(sc, 4), sc["x"], BARS[prec])
     s.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 511, 512, 513, 1500])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_read_returns_every_row_in_input_order(ctx, mp, prec, n):
+    """Load and read at the edges of a wavefront and of the read's workgroup
+    pass, before and after a reorder, all fields or some: the inputs come back
+    row by row (values that FP32 holds, so exactly) and in place, and nothing
+    past the last row is written."""
+    import torch
+    sc = scenes.random_block(n_cells=(6, 6, 6), mesh_cells=(12, 10, 9), seed=62, vel=0.3, stress_scale=2e3)
+    pick = np.random.default_rng(n).permutation(len(sc["x"]))[:n]
+    sc.update({k: np.ascontiguousarray(sc[k][pick]) for k in ("x", "v", "stress", "vol", "mass")})
+    s = ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32)
+    want = {k: sc[k] for k in ("x", "v", "stress", "vol")}
+    c = np.floor(sc["x"] / sc["mesh"]["h"]).astype(np.int64)
+    want["cell"] = (c[:, 0] + 12 * (c[:, 1] + 10 * c[:, 2])).astype(np.int32)
+    for k, a in s.read().items():
+        np.testing.assert_array_equal(a, want[k], err_msg=k)
+    s.step(1)
+    host = s.read()
+    check(f"read/{n}/{prec}", host, oracle.run(sc, 1), sc["x"], BARS[prec])
+    for fields in (("x", "v", "stress", "vol", "cell"), ("stress",), ("cell", "x")):
+        pad = {k: torch.full((np.asarray(host[k]).size + 8,), -7, dtype=torch.int32 if k == "cell" else torch.float64,
+                             device="cuda") for k in fields}
+        torch.cuda.synchronize()
+        s.read(device_out=pad)
+        for k in fields:
+            got = pad[k].cpu().numpy()
+            np.testing.assert_array_equal(got[:-8], np.asarray(host[k]).reshape(-1), err_msg=k)
+            assert (got[-8:] == -7).all(), k
+    s.destroy()
