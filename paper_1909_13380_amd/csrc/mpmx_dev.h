@@ -27,6 +27,8 @@ constexpr int kBrickCells = 64;           // cells per brick
 constexpr int kChunk = 512;               // max particles per work item
 constexpr int kXcds = 8;                  // accelerator dies (one L2 each) of the GPU
 constexpr int kBlock = 1024;              // threads per workgroup of the reorder and control kernel
+constexpr int kSortThreads = 256;         // threads per workgroup of the reorder phases launched one by one
+constexpr int kSortBricks = 32;           // fewest bricks per workgroup of their scan
 constexpr int kSortU = 4;                 // particles per lane in flight in the reorder's particle phases
 constexpr int kLoadThreads = 256;         // threads per workgroup of the particle load
 constexpr int kReadThreads = 256;         // threads per workgroup of the particle read

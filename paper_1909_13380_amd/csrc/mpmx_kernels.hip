@@ -1912,14 +1912,14 @@ struct MoveRec {
 // distinct cells, so the scatter kernels' LDS atomics for one node corner do
 // not collide.  Each pass reads kMoveLevels levels before it writes any.
 // Resets the brick's per-cell counts for the next sort.
-// A chunk is the listed bricks [i0, i1).
+// The calling wavefront takes the listed bricks first, first + step, ...
+// below end.
 template <typename R>
-__device__ void sort_move(const BatchDev &B, uint32_t i0, uint32_t i1)
+__device__ void sort_move(const BatchDev &B, uint32_t first, uint32_t step, uint32_t end)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const uint32_t nw = blockDim.x >> 6;
-    for (uint32_t i = i0 + uni(threadIdx.x >> 6); i < i1; i += nw) {
+    for (uint32_t i = first; i < end; i += step) {
         const uint32_t gb = uni(gp(B.bricks)[i]);
         const int s = find_scene_u(B.boffs, B.nscenes, gb);
         const SortView sv = sort_view(B, s);
@@ -2026,7 +2026,9 @@ __global__ void __launch_bounds__(kBlock) k_reorder(BatchDev B)
     const uint32_t mpass = blockDim.x >> 6;
     const uint32_t mch = max(1u, (nbr + mpass * (uint32_t)target - 1) / (mpass * (uint32_t)target)) * mpass;
     const uint32_t nmc = max(1u, (nbr + mch - 1) / mch);
-    run_chunks(F, PH_MOVE, nmc, go, &sh, [&](uint32_t c) { sort_move<R>(B, c * mch, min((c + 1) * mch, nbr)); });
+    run_chunks(F, PH_MOVE, nmc, go, &sh, [&](uint32_t c) {
+        sort_move<R>(B, c * mch + uni(threadIdx.x >> 6), mpass, min((c + 1) * mch, nbr));
+    });
     // the last workgroup to leave runs the step control
     if (threadIdx.x == 0) {
         __threadfence();
@@ -2036,6 +2038,52 @@ __global__ void __launch_bounds__(kBlock) k_reorder(BatchDev B)
     if (!sh)
         return;
     __threadfence();
+    step_control(B);
+}
+
+// The same phases as launches of their own, for the steps the host knows to
+// reorder (a scene's first step, and every step of a scene that always
+// sorts).  The kernel boundary (1.7 us in a graph) then orders the phases in
+// place of a grid barrier among 256 workgroups (13 us with its fences), and
+// the phases run on grids of small workgroups: 524k particles 119 -> 50 us.
+// Steps that may or may not reorder keep the single launch, which costs one
+// boundary when nothing moves.
+__global__ void __launch_bounds__(kSortThreads) k_sort_count(BatchDev B)
+{
+    if (B.flags[BF_ANY_SORT])
+        sort_count(B, blockIdx.x, gridDim.x);
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_bricks(BatchDev B, uint32_t bch)
+{
+    const uint32_t nb = (uint32_t)B.total_bricks;
+    if (B.flags[BF_ANY_SORT])
+        sort_bricks(B, blockIdx.x, min(blockIdx.x * bch, nb), min((blockIdx.x + 1) * bch, nb));
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_scan(BatchDev B, uint32_t bch)
+{
+    const uint32_t nb = (uint32_t)B.total_bricks;
+    if (B.flags[BF_ANY_SORT])
+        scan_finish(B, blockIdx.x, min(blockIdx.x * bch, nb), min((blockIdx.x + 1) * bch, nb));
+}
+
+__global__ void __launch_bounds__(kSortThreads) k_sort_perm(BatchDev B)
+{
+    if (B.flags[BF_ANY_SORT])
+        sort_perm(B, blockIdx.x, gridDim.x);
+}
+
+template <typename R>
+__global__ void __launch_bounds__(kSortThreads) k_sort_move(BatchDev B)
+{
+    const uint32_t nw = blockDim.x >> 6;
+    if (B.flags[BF_ANY_SORT])
+        sort_move<R>(B, blockIdx.x * nw + uni(threadIdx.x >> 6), gridDim.x * nw, uni(B.flags[BF_NBRICKS]));
+}
+
+__global__ void __launch_bounds__(kBlock) k_control(BatchDev B)
+{
     step_control(B);
 }
 
@@ -3831,6 +3879,7 @@ static KernelSet make_set()
     k.read_out = (const void *)&k_read_out<R>;
     k.nodes_out = (const void *)&k_nodes_out<R>;
     k.reorder = (const void *)&k_reorder<R>;
+    k.sort_move = (const void *)&k_sort_move<R>;
     set_items<R, SH, 0>(k);
     set_items<R, SH, 1>(k);
     set_items<R, SH, 2>(k);
@@ -3846,7 +3895,9 @@ const KernelSet &kernel_set(int prec, int shape)
 
 const CommonKernels &common_kernels()
 {
-    static const CommonKernels c = {(const void *)&k_begin, (const void *)&k_cell_counts};
+    static const CommonKernels c = {(const void *)&k_begin,       (const void *)&k_cell_counts, (const void *)&k_sort_count,
+                                    (const void *)&k_sort_bricks, (const void *)&k_sort_scan,   (const void *)&k_sort_perm,
+                                    (const void *)&k_control};
     return c;
 }
 

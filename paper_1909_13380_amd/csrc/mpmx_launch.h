@@ -16,6 +16,7 @@ struct KernelSet {
     const void *read_out;   // (const SceneDev*, x, v, sig, vol, cell)
     const void *nodes_out;  // (const SceneDev*, m, p, f)
     const void *reorder;    // (BatchDev): reorder, then the step control
+    const void *sort_move;  // (BatchDev): the reorder's last phase as a launch of its own
     const void *p2g[kNumItemThreadChoices];      // (BatchDev)
     const void *stress[kNumItemThreadChoices];   // (BatchDev)
     const void *g2p_p2g[kNumItemThreadChoices];  // (BatchDev)
@@ -29,6 +30,12 @@ struct KernelSet {
 struct CommonKernels {
     const void *begin;        // (BatchDev, const int64_t*)
     const void *cell_counts;  // (const SceneDev*, uint32_t*)
+    // the reorder's other phases and the step control as launches of their own
+    const void *sort_count;   // (BatchDev)
+    const void *sort_bricks;  // (BatchDev, bricks per workgroup)
+    const void *sort_scan;    // (BatchDev, bricks per workgroup)
+    const void *sort_perm;    // (BatchDev)
+    const void *control;      // (BatchDev)
 };
 
 const KernelSet &kernel_set(int prec, int shape);

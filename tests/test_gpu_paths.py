@@ -88,3 +88,31 @@ def test_read_returns_every_row_in_input_order(ctx, mp, prec, n):
             np.testing.assert_array_equal(got[:-8], np.asarray(host[k]).reshape(-1), err_msg=k)
             assert (got[-8:] == -7).all(), k
     s.destroy()
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_known_reorders_run_phase_by_phase(ctx, mp, noalloc):
+    """Scenes whose reorder the host knows of (fresh, or always sorting) in
+    batches with ones it does not know of, an empty one and one asked for no
+    steps, over three calls: each equals the oracle, and each always-sorting
+    scene counts a reorder per step."""
+    cells = [(9, 7, 6), (3, 3, 2), (5, 6, 4), (2, 2, 2), (4, 3, 3)]
+    scs = [scenes.random_block(n_cells=c, mesh_cells=tuple(3 * k + 5 for k in c), seed=70 + i, vel=1.0, stress_scale=1e3)
+           for i, c in enumerate(cells)]
+    for k in ("x", "v", "stress", "vol", "mass"):
+        scs[3][k] = scs[3][k][:0]
+    always = [False, True, False, False, True]
+    ss = [ctx.create_scene(sc, precision=mp.FP64, sort_policy=mp.SORT_ALWAYS if a else mp.SORT_ON_DEMAND)
+          for sc, a in zip(scs, always)]
+    steps = [[3, 2, 0, 2, 0], [0, 4, 5, 3, 0], [6, 3, 2, 1, 4]]
+    for call in steps:
+        (ctx.batch_step_noalloc if noalloc else ctx.batch_step)(ss, call)
+    for i, (sc, s, a) in enumerate(zip(scs, ss, always)):
+        k = sum(call[i] for call in steps)
+        st = s.stats()
+        assert st["error_bits"] == 0 and st["steps_done"] == k, (i, st)
+        if a:
+            assert st["n_sorts"] == k, (i, st)
+        if len(sc["x"]):
+            check(f"known-reorders/{i}/{noalloc}", s.read(), oracle.run(sc, k), sc["x"], BARS["fp64"])
+        s.destroy()
