@@ -2540,26 +2540,26 @@ __global__ void __launch_bounds__(T) k_stress(BatchDev B)
         const Parts<R> P = parts<R>(S, cur);
         const NodeBuf<R> nb = node_buf<R>(S, buf);
         uint32_t pcell[KP];
-        int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
 #pragma unroll
-        for (int rr = 0; rr < KP; ++rr) {
-            const uint32_t q = threadIdx.x + rr * T;
-            if (q >= item.count)
-                continue;
-            pcell[rr] = ldg(P.cell, item.start + q);
-            int c[3];
-            unpack_cell(pcell[rr], c);
-            for (int a = 0; a < 3; ++a) {
-                mn[a] = min(mn[a], c[a]);
-                mx[a] = max(mx[a], c[a]);
-            }
-        }
+        for (int rr = 0; rr < KP; ++rr)
+            pcell[rr] = ldg(P.cell, item.start + min((uint32_t)threadIdx.x + rr * T, item.count - 1u));
         // the node box: recorded by the kernel that filled this node buffer
-        // when the items are unchanged since, else reduced here
+        // when the items are unchanged since, else reduced here.  With a
+        // recorded box nothing waits for the cells before the node tile's
+        // loads leave (2.1M particles: 47.0 -> 45.9 us)
         Tile t;
         if (cld(&S.ctl[CTL_BOX_OK])) {
             t = cld_struct(&pick(S.tiles, buf)[r.it]);
         } else {
+            int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
+            for (int rr = 0; rr < KP; ++rr) {   // (lanes past the item's end hold its last particle)
+                int c[3];
+                unpack_cell(pcell[rr], c);
+                for (int a = 0; a < 3; ++a) {
+                    mn[a] = min(mn[a], c[a]);
+                    mx[a] = max(mx[a], c[a]);
+                }
+            }
             int blo[3], bhi[3];
             item_box<T>(mn, mx, red, blo, bhi);
             t = tile_of_cells<SH>(blo, bhi);
