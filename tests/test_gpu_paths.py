@@ -116,3 +116,22 @@ def test_known_reorders_run_phase_by_phase(ctx, mp, noalloc):
         if len(sc["x"]):
             check(f"known-reorders/{i}/{noalloc}", s.read(), oracle.run(sc, k), sc["x"], BARS["fp64"])
         s.destroy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("algo", [scenes.USF, scenes.USL, scenes.MUSL])
+def test_isoparametric_location_of_fast_particles(ctx, mp, algo, prec):
+    """A body that crosses most of a cell per step on strongly distorted
+    cells: the location of a moved particle starts from the step matrix of
+    its previous place, far from the new one, or walks into another cell."""
+    base = scenes.random_block(n_cells=(6, 6, 5), mesh_cells=(16, 12, 10), h=0.05, seed=63, vel=2.0, dt=1e-4,
+                               material=scenes.drucker_prager(psi_deg=5, c=1e3), stress_scale=2e3,
+                               bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE))
+    base["x"] = base["x"] + np.array([0.0, 0.0, 0.1])
+    base["v"] = base["v"] + np.array([400.0, -150.0, 90.0])
+    base["scheme"]["algo"] = algo
+    sc = scenes.distort(base, amp=0.35, seed=64)
+    s = ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32)
+    s.step(3)
+    check(f"iso-fast/{algo}/{prec}", s.read(), oracle.run(sc, 3), sc["x"], BARS[prec])
+    s.destroy()
