@@ -241,7 +241,11 @@ const char *mpmx_last_error(const mpmx_ctx *ctx);
  *                          recorded by its first call of more than one step
  *                          (after tuning, when that call tunes), so later
  *                          calls only replay it.  Graphs are not used while
- *                          per-kernel profiling is on.
+ *                          per-kernel profiling is on, nor for USF batches
+ *                          of at most about one work item (512 particles)
+ *                          per compute unit, whose steps run in launches of
+ *                          many steps each (unless this is 0 or autotuning
+ *                          is off).
  *   MPMX_OPT_AUTOTUNE      1 (default): on the first call that runs at least
  *                          MPMX_TUNE_MIN_STEPS steps on a batch layout
  *                          (precision, shape function, algorithm and the

@@ -79,6 +79,7 @@ struct Batch {
     BatchDev bd{};
     int prec = 0, shape = 0, algo = 0;
     bool always = false;    // some scene reorders after every step
+    int64_t items = 0;      // sum of the scenes' items
     // the last queued steps of this batch (its image is free to rewrite
     // once they are done)
     std::shared_ptr<StepEvent> last_use;
@@ -172,6 +173,7 @@ struct Scene {
     std::shared_ptr<StepEvent> last;
     bool main_sync = false;
     bool fresh = true;       // no steps queued yet: its first step reorders
+    int64_t items = 0;       // work items of the particles as loaded (estimate)
 };
 
 }  // namespace
@@ -534,7 +536,7 @@ int build_batch(mpmx_ctx *ctx, Batch &b, const std::vector<Scene *> &list)
                  o_co = o_io + 4 * n1, o_fl = (o_co + 4 * n1 + 127) & ~(size_t)127, o_sc = o_fl + 4 * BF_WORDS,
                  o_br = o_sc + 16 * (size_t)kScanChunks, total = o_br + 4 * (size_t)std::max<int64_t>(nbr, 1);
     std::vector<uint8_t> img(total, 0);
-    int64_t maxit = 0, *po = (int64_t *)(img.data() + o_po), *bo = (int64_t *)(img.data() + o_bo);
+    int64_t maxit = 0, items = 0, *po = (int64_t *)(img.data() + o_po), *bo = (int64_t *)(img.data() + o_bo);
     SceneDev **sp = (SceneDev **)img.data();
     uint32_t **cp = (uint32_t **)(img.data() + o_ct);
     for (int i = 0; i < n; ++i) {
@@ -543,7 +545,9 @@ int build_batch(mpmx_ctx *ctx, Batch &b, const std::vector<Scene *> &list)
         po[i + 1] = po[i] + list[i]->h.np;
         bo[i + 1] = bo[i] + list[i]->h.nbricks;
         maxit += list[i]->h.max_items;
+        items += list[i]->items;
     }
+    b.items = items;
     b.always = std::any_of(list.begin(), list.end(), [](const Scene *sc) { return sc->h.sort_always != 0; });
     if (total > b.dcap) {
         if (b.dmem)
@@ -692,6 +696,42 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
         return rc;
     if (ev)
         HIPCHK(ctx, hipEventRecord(ev[2], st));
+    return MPMX_OK;
+}
+
+// USF batches of at most one item per compute unit run their steps (but the
+// first of a call, which knows of fresh scenes) in launches of k_steps: there
+// a step costs two barriers in place of three launches.  Time per step
+// (linear, FP32, us), in a launch of its own kernels and in k_steps:
+//   1000 particles, 8 items 18.9, 14.6; 51200, 100 items 22.0, 16.8;
+//   110592, 216 items 22.2, 18.1; 147456, 288 items 23.8, 30.0;
+//   262144, 512 items 29.0, 32.2.
+// Beyond one item per workgroup the separate kernels win, with several
+// smaller workgroups resident on each compute unit.  The host knows the
+// particles' extent as loaded; items that a spreading body adds later make a
+// step slower, not wrong.  Calls of fewer than three steps have nothing to
+// share; profiled, always-sorting and fixed-shape (no autotuning or graphs)
+// calls keep one launch per kernel.
+constexpr int64_t kStepsPerLaunch = 1024;
+
+bool steps_at_once(const mpmx_ctx *ctx, const Batch &b)
+{
+    return ctx->autotune && ctx->graph_steps > 0 && !ctx->prof.on && b.algo == MPMX_USF && !b.always &&
+           b.items <= ctx->num_cu;
+}
+
+int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)
+{
+    const KernelSet &K = kernel_set(b.prec, b.shape);
+    BatchDev bd = b.bd;
+    const dim3 grid((unsigned)std::clamp<int64_t>(bd.max_items, 1, ctx->num_cu)), t(kStepThreads);
+    while (left > 0) {
+        uint32_t n = (uint32_t)std::min(left, kStepsPerLaunch);
+        void *args[] = {&bd, &n};
+        if (int rc = launch(ctx, "steps", K.steps, grid, t, args))
+            return rc;
+        left -= n;
+    }
     return MPMX_OK;
 }
 
@@ -921,6 +961,11 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
     }
     ctx->last = cfg;
     const int K = ctx->graph_steps;
+    if (left >= 2 && steps_at_once(ctx, b)) {
+        if ((rc = enqueue_steps(ctx, b, left)))
+            return rc;
+        return mark_queued(ctx, b);
+    }
     // the K-step graph is recorded by the first call of more than one step
     // with this launch shape (recording runs nothing), so that later calls
     // only replay it, however few steps this one has left
@@ -1419,6 +1464,8 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
     uint32_t ctl[CTL_WORDS] = {0};
     ctl[CTL_NEED_SORT] = 1;
     ctl[CTL_ALGO] = (uint32_t)h.algo;
+    for (int a = 0; a < 3; ++a)
+        ctl[CTL_LOW + a] = (uint32_t)std::numeric_limits<int>::max();
     if (ok && hipMemcpy(h.ctl, ctl, sizeof ctl, hipMemcpyHostToDevice) != hipSuccess)
         ok = false;
     if (ok && hipMemcpy(s->d, &h, sizeof(SceneDev), hipMemcpyHostToDevice) != hipSuccess)
@@ -1444,6 +1491,13 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
         free_scene(ctx, s);
         return fail(ctx, err_code(ctl[CTL_ERR]), "input particle outside the mesh or not finite (bits %u)",
                     ctl[CTL_ERR]);
+    }
+    // items of the loaded particles, if they fill the bricks of their extent
+    if (np > 0) {
+        int64_t bricks = 1;
+        for (int a = 0; a < 3; ++a)
+            bricks *= ceil_div((int64_t)ctl[CTL_TOP + a] - (int64_t)ctl[CTL_LOW + a] + 1, kBrick);
+        s->items = std::max(std::min(bricks, np), ceil_div(np, kChunk));
     }
     std::vector<Scene *> one{s};
     rc = build_batch(ctx, s->single, one);

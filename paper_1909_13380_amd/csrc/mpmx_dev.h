@@ -29,6 +29,7 @@ constexpr int kXcds = 8;                  // accelerator dies (one L2 each) of t
 constexpr int kBlock = 1024;              // threads per workgroup of the reorder and control kernel
 constexpr int kSortThreads = 256;         // threads per workgroup of the reorder phases launched one by one
 constexpr int kSortBricks = 32;           // fewest bricks per workgroup of their scan
+constexpr int kStepThreads = 512;         // threads per workgroup of k_steps: one particle each
 constexpr int kSortU = 4;                 // particles per lane in flight in the reorder's particle phases
 constexpr int kLoadThreads = 256;         // threads per workgroup of the particle load
 constexpr int kReadThreads = 256;         // threads per workgroup of the particle read
@@ -62,7 +63,10 @@ enum Ctl : int {
     CTL_BOX_OK = 13,    // tiles[CTL_NBUF] holds this step's node box of every item
     CTL_ALGO = 14,      // the scene's algorithm (0 USF, 1 USL), set at creation
     CTL_LOST = 15,      // particles found outside the mesh (the scene stops on the first)
-    CTL_WORDS = 16
+    CTL_STEP_WORDS = 16,   // the words above: what the step control reads and writes
+    CTL_LOW = 16,       // + a: smallest cell of the loaded particles
+    CTL_TOP = 19,       // + a: largest
+    CTL_WORDS = 24
 };
 
 // ERR_TILE: an item's particles spread beyond the LDS node tile, which the
@@ -156,7 +160,21 @@ enum BatchFlag : int {
     BF_CLAIM = 96,        // + 32 p: chunks of reorder phase p claimed
     BF_DONE = 96 + 32 * 5,          // + 32 p: chunks of reorder phase p done
     BF_RELEASE = 96 + 64 * 5,       // + 32 g: reorder phases complete, polled by group g
-    BF_WORDS = 96 + 64 * 5 + 32 * kXcds
+    BF_WORDS = 96 + 64 * 5 + 32 * kXcds,
+    // k_steps uses the same lines between reorders: workgroups started; the
+    // list published last (its number and, above, its workgroups; 64-bit),
+    // what goes with it (barriers passed and events; 64-bit) and the steps
+    // left; the barrier's arrivals of groups (and events; 64-bit) and per
+    // group; the release word (barriers and events; 64-bit) polled by group
+    // g; workgroups finished
+    BF_STEP_START = BF_EXIT,
+    BF_STEP_LIST = BF_CLAIM,
+    BF_STEP_INFO = BF_CLAIM + 2,
+    BF_STEP_LEFT = BF_CLAIM + 4,
+    BF_STEP_EXIT = BF_CLAIM + 34,
+    BF_STEP_ROOT = BF_CLAIM + 32,
+    BF_STEP_GROUP = BF_CLAIM + 64,      // + 32 g
+    BF_STEP_RELEASE = BF_RELEASE        // + 32 g
 };
 
 // A launch over several scenes: work is flattened over scenes in order.

@@ -238,6 +238,37 @@ struct alignas(2 * sizeof(R)) R2 {
     R s, t;
 };
 
+// How a kernel reads nodes.  PLAIN: the data come from earlier kernels.
+// SHARED: other workgroups of this kernel wrote them (k_steps), so loads and
+// stores are agent-scope atomics, which no stale cache line can serve.
+enum Nodes : int { PLAIN = 0, SHARED = 1 };
+
+template <Nodes M, typename T>
+__device__ inline T ldn(const GLOBAL T *b, uint32_t i)
+{
+    const GLOBAL T *q = (const GLOBAL T *)((const GLOBAL char *)b + i * (uint32_t)sizeof(T));
+    if constexpr (M == SHARED)
+        return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        return *q;
+}
+
+template <Nodes M, typename T>
+__device__ inline T ldn(const Comp<T> &c, uint32_t i)
+{
+    return ldn<M>((const GLOBAL T *)c.base, c.off + i);
+}
+
+template <Nodes M, typename T>
+__device__ inline void stn(GLOBAL T *b, uint32_t i, T v)
+{
+    GLOBAL T *q = (GLOBAL T *)((GLOBAL char *)b + i * (uint32_t)sizeof(T));
+    if constexpr (M == SHARED)
+        __hip_atomic_store(q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *q = v;
+}
+
 // Component arrays of one node buffer.
 template <typename R>
 struct NodeBuf {
@@ -281,20 +312,21 @@ __device__ inline void velocity_from_raw(const SceneDev &S, double m, const R p[
     }
 }
 
-template <typename R>
+template <typename R, Nodes M = PLAIN>
 __device__ inline void node_velocity(const SceneDev &S, const NodeBuf<R> &nb, int i, int j, int k, R v[3])
 {
     const uint32_t I = node_id(S, i, j, k);
-    const R p[3] = {ldg(nb.p[0], I), ldg(nb.p[1], I), ldg(nb.p[2], I)};
-    velocity_from_raw<R>(S, ldg(nb.m, I), p, i, j, k, v);
+    const R p[3] = {ldn<M>(nb.p[0], I), ldn<M>(nb.p[1], I), ldn<M>(nb.p[2], I)};
+    velocity_from_raw<R>(S, ldn<M>((const GLOBAL double *)nb.m, I), p, i, j, k, v);
 }
 
-// Factor of the external nodal forces in the scene's current step n (the
-// step control has counted it in CTL_STEPS): the smooth ramp u^2 (3 - 2u),
-// u = n / force_ramp, and 1 from step force_ramp on.
-__device__ inline double external_force_scale(const SceneDev &S)
+// Factor of the external nodal forces in the scene's current step n (by
+// default the one the step control has counted in CTL_STEPS): the smooth ramp
+// u^2 (3 - 2u), u = n / force_ramp, and 1 from step force_ramp on.
+__device__ inline double external_force_scale(const SceneDev &S, int64_t n = -1)
 {
-    const int64_t n = (int64_t)__hip_atomic_load(&S.ctl[CTL_STEPS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n < 0)
+        n = (int64_t)__hip_atomic_load(&S.ctl[CTL_STEPS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (S.force_ramp <= 0 || n >= S.force_ramp)
         return 1.0;
     const double u = (double)n / (double)S.force_ramp;
@@ -306,7 +338,7 @@ __device__ inline double external_force_scale(const SceneDev &S)
 // the node's mass, momentum and force.
 template <typename R>
 __device__ inline void update_from_raw(const SceneDev &S, double m, const R p[3], const R f[3], int i, int j, int k,
-                                       R a[3], R vn[3])
+                                       R a[3], R vn[3], int64_t step = -1)
 {
     const double inv = m > S.eps_m ? 1.0 / m : 0.0;   // void node: v = a = 0
     uint32_t em = 0u;
@@ -317,7 +349,7 @@ __device__ inline void update_from_raw(const SceneDev &S, double m, const R p[3]
     }
     // a node's external force (ramped over the scene's first steps) joins
     // the particles' sum before a = f / m; CTL_STEPS is the running step
-    const double fs = (em & 8u) ? external_force_scale(S) : 0.0;
+    const double fs = (em & 8u) ? external_force_scale(S, step) : 0.0;
     R v[3];
     for (int c = 0; c < 3; ++c) {
         v[c] = (R)((double)p[c] * inv);
@@ -346,13 +378,14 @@ __device__ inline void update_from_raw(const SceneDev &S, double m, const R p[3]
     }
 }
 
-template <typename R>
-__device__ inline void node_update(const SceneDev &S, const NodeBuf<R> &nb, int i, int j, int k, R a[3], R vn[3])
+template <typename R, Nodes M = PLAIN>
+__device__ inline void node_update(const SceneDev &S, const NodeBuf<R> &nb, int i, int j, int k, R a[3], R vn[3],
+                                   int64_t step = -1)
 {
     const uint32_t I = node_id(S, i, j, k);
-    const R p[3] = {ldg(nb.p[0], I), ldg(nb.p[1], I), ldg(nb.p[2], I)};
-    const R f[3] = {ldg(nb.f[0], I), ldg(nb.f[1], I), ldg(nb.f[2], I)};
-    update_from_raw<R>(S, ldg(nb.m, I), p, f, i, j, k, a, vn);
+    const R p[3] = {ldn<M>(nb.p[0], I), ldn<M>(nb.p[1], I), ldn<M>(nb.p[2], I)};
+    const R f[3] = {ldn<M>(nb.f[0], I), ldn<M>(nb.f[1], I), ldn<M>(nb.f[2], I)};
+    update_from_raw<R>(S, ldn<M>((const GLOBAL double *)nb.m, I), p, f, i, j, k, a, vn, step);
 }
 
 // ------------------------------------------------------ shape functions --
@@ -849,6 +882,18 @@ __device__ inline T *uni(T *p)
     return (T *)(((uint64_t)uni((uint32_t)(v >> 32)) << 32) | (uint64_t)uni((uint32_t)v));
 }
 
+// A word that another workgroup of this kernel may write (agent scope; the
+// address is wave-uniform).
+__device__ inline uint32_t live(const uint32_t *p)
+{
+    return uni(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+__device__ inline void set_live(uint32_t *p, uint32_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Load through the scalar cache: the address is wave-uniform and the data
 // does not change during the kernel (written at creation or by an earlier
 // kernel).
@@ -1063,7 +1108,7 @@ __device__ inline void item_box(const int mn[3], const int mx[3], int *red, int 
 }
 
 // Zero node buffer `buf` over the given node box.
-template <typename R>
+template <typename R, Nodes M = PLAIN>
 __device__ inline void clear_box(const SceneDev &S, const NodeBuf<R> &nb, const Tile &t)
 {
     const int vol = t.dim[0] * t.dim[1] * t.dim[2];
@@ -1074,10 +1119,10 @@ __device__ inline void clear_box(const SceneDev &S, const NodeBuf<R> &nb, const 
         else
             tile_node(t, q, i, j, k);
         const uint32_t I = node_id(S, i, j, k);
-        stg(nb.m, I, 0.0);
+        stn<M>(nb.m, I, 0.0);
         for (int a = 0; a < 3; ++a) {
-            stg(nb.p[a], I, (R)0);
-            stg(nb.f[a], I, (R)0);
+            stn<M>(nb.p[a].base, nb.p[a].off + I, (R)0);
+            stn<M>(nb.f[a].base, nb.f[a].off + I, (R)0);
         }
     }
 }
@@ -1145,7 +1190,7 @@ __global__ void __launch_bounds__(kLoadThreads) k_load(SceneDev *Sd, const doubl
     R *SG = (R *)S.sig[0];
     R *VO = (R *)S.vol[0];
     R *M = (R *)S.mass[0];
-    int mn[3] = {INT_MAX, INT_MAX, INT_MAX};
+    int mn[3] = {INT_MAX, INT_MAX, INT_MAX}, mx[3] = {-1, -1, -1};
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
         // every input of the particle in one round trip (the compiler cannot
         // tell the stored arrays from the loaded ones)
@@ -1195,27 +1240,41 @@ __global__ void __launch_bounds__(kLoadThreads) k_load(SceneDev *Sd, const doubl
         S.cell[0][p] = pack_cell(c);
         S.pid[0][p] = (uint32_t)p;
         if (!e)
-            for (int a = 0; a < 3; ++a)
+            for (int a = 0; a < 3; ++a) {
                 mn[a] = min(mn[a], c[a]);
+                mx[a] = max(mx[a], c[a]);
+            }
     }
-    // the smallest cell per axis (sets the brick shift): one atomic per
-    // workgroup, and only where it lowers the value read before it.  One per
+    // the smallest cell per axis (sets the brick shift) and the largest: one
+    // atomic per workgroup, and only where it changes the value read before it.  One per
     // wavefront and axis, all on one cache line, set this kernel's time
     // (1950 us for 2.1M particles).
-    __shared__ int low[3][kLoadThreads / 64];
+    __shared__ int ext[6][kLoadThreads / 64];
     for (int a = 0; a < 3; ++a) {
-        const int w = wave_reduce<false>(mn[a]);
-        if ((threadIdx.x & 63) == 0)
-            low[a][threadIdx.x >> 6] = w;
+        const int lo = wave_reduce<false>(mn[a]), hi = wave_reduce<true>(mx[a]);
+        if ((threadIdx.x & 63) == 0) {
+            ext[a][threadIdx.x >> 6] = lo;
+            ext[3 + a][threadIdx.x >> 6] = hi;
+        }
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
-        int w = INT_MAX;
-        for (int q = 0; q < kLoadThreads / 64; ++q)
-            w = min(w, low[threadIdx.x][q]);
-        int *to = &Sd->cmin[threadIdx.x];
-        if (w < __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMin(to, w);
+    if (threadIdx.x < 6) {
+        const int a = threadIdx.x % 3;
+        int w = ext[threadIdx.x][0];
+        for (int q = 1; q < kLoadThreads / 64; ++q)
+            w = threadIdx.x < 3 ? min(w, ext[threadIdx.x][q]) : max(w, ext[threadIdx.x][q]);
+        if (threadIdx.x < 3) {
+            int *to = &Sd->cmin[a];
+            if (w < __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMin(to, w);
+            to = (int *)&S.ctl[CTL_LOW + a];
+            if (w < __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMin(to, w);
+        } else {
+            int *to = (int *)&S.ctl[CTL_TOP + a];
+            if (w > __hip_atomic_load(to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                atomicMax(to, w);
+        }
     }
 }
 
@@ -1389,8 +1448,8 @@ __device__ void step_control(const BatchDev &B)
         uint32_t items = 0, clears = 0;
         if (s < B.nscenes) {
             uint4 *blk = (uint4 *)B.ctls[s];
-            uint32_t c[CTL_WORDS];
-            for (int q = 0; q < CTL_WORDS / 4; ++q) {
+            uint32_t c[CTL_STEP_WORDS];
+            for (int q = 0; q < CTL_STEP_WORDS / 4; ++q) {
                 const uint4 w = blk[q];
                 c[4 * q] = w.x;
                 c[4 * q + 1] = w.y;
@@ -1432,7 +1491,7 @@ __device__ void step_control(const BatchDev &B)
                 items = c[CTL_N_ITEMS];
                 clears = c[CTL_NBUF] ? c[CTL_ACC0] : c[CTL_ACC1];   // boxes of the other buffer
             }
-            for (int q = 0; q < CTL_WORDS / 4; ++q)
+            for (int q = 0; q < CTL_STEP_WORDS / 4; ++q)
                 blk[q] = uint4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
         }
         // inclusive scan over the workgroup: waves, then wave totals
@@ -1602,8 +1661,9 @@ __device__ inline SortView sort_view(const BatchDev &B, int s)
     v.S = S;
     uint32_t *ctl = cld(&S->ctl);
     v.ctl = gp(ctl);
-    v.cur = (int)cld(&ctl[CTL_CUR]);
-    v.sorting = cld(&ctl[CTL_ERR]) == 0u && cld(&ctl[CTL_REMAIN]) > 0u && cld(&ctl[CTL_NEED_SORT]) != 0u;
+    // (k_steps reorders more than once in a launch: no cached copy)
+    v.cur = (int)live(&ctl[CTL_CUR]);
+    v.sorting = live(&ctl[CTL_ERR]) == 0u && live(&ctl[CTL_REMAIN]) > 0u && live(&ctl[CTL_NEED_SORT]) != 0u;
     v.cell = gp((const uint32_t *)cld(&S->cell[v.cur]));
     v.cnt = gp(cld(&S->cnt));
     v.cstart = gp(cld(&S->cstart));
@@ -1798,10 +1858,10 @@ __device__ void sort_bricks(const BatchDev &B, uint32_t j, uint32_t b0, uint32_t
     __syncthreads();   // wseg is reused by the workgroup's next chunk
 }
 
-// Workgroup-wide inclusive scan of Seg values with seg_join.
-__device__ inline Seg block_seg_scan(Seg v)
+// Workgroup-wide inclusive scan of Seg values with seg_join; sv (one entry per
+// thread, in LDS) holds the results.
+__device__ inline Seg block_seg_scan(Seg v, Seg *sv)
 {
-    __shared__ Seg sv[kBlock];
     sv[threadIdx.x] = v;
     __syncthreads();
     for (int o = 1; o < (int)blockDim.x; o <<= 1) {
@@ -1823,7 +1883,7 @@ __device__ inline Seg block_seg_scan(Seg v)
 // brick count from all of them), then every brick's exclusive particle and
 // item start, each scene's totals, and the batch's list of non-empty bricks
 // in brick order.
-__device__ void scan_finish(const BatchDev &B, uint32_t j, uint32_t b0, uint32_t b1)
+__device__ void scan_finish(const BatchDev &B, uint32_t j, uint32_t b0, uint32_t b1, Seg *sv)
 {
     __shared__ uint32_t red[kBlock / 64][3];
     __shared__ uint32_t carry[3];
@@ -1885,14 +1945,11 @@ __device__ void scan_finish(const BatchDev &B, uint32_t j, uint32_t b0, uint32_t
             mine.n += bc ? 1u : 0u;
         }
     });
-    const Seg inc = block_seg_scan(mine);
+    block_seg_scan(mine, sv);
     // exclusive start of the run: carried prefix joined with the earlier threads
-    __shared__ Seg xs[kBlock];
-    xs[threadIdx.x] = inc;
-    __syncthreads();
     Seg run{carry[0], carry[1], 0u, carry[2]};
     if (threadIdx.x > 0)
-        run = seg_join(run, xs[threadIdx.x - 1]);
+        run = seg_join(run, sv[threadIdx.x - 1]);
     __syncthreads();
     walk_run(B, r, [&](const SceneDev *S, bool sorting, uint32_t gb, uint32_t b, bool first, bool last) {
         if (first)
@@ -2073,6 +2130,7 @@ template <typename R>
 __global__ void __launch_bounds__(kBlock) k_reorder(BatchDev B)
 {
     __shared__ int sh;
+    __shared__ Seg sv[kBlock];
     if (!B.flags[BF_ANY_SORT]) {
         // nothing moves: the first workgroup runs the step control alone
         if (blockIdx.x == 0)
@@ -2100,7 +2158,7 @@ __global__ void __launch_bounds__(kBlock) k_reorder(BatchDev B)
                [&](uint32_t c) { sort_bricks(B, c, min(c * bch, nb), min((c + 1) * bch, nb)); });
     go = phase_done(F, PH_BRICKS, &sh);
     run_chunks(F, PH_SCAN, nbc, go, &sh,
-               [&](uint32_t c) { scan_finish(B, c, min(c * bch, nb), min((c + 1) * bch, nb)); });
+               [&](uint32_t c) { scan_finish(B, c, min(c * bch, nb), min((c + 1) * bch, nb), sv); });
     go = phase_done(F, PH_SCAN, &sh);
     run_chunks(F, PH_PERM, npc, go, &sh, [&](uint32_t c) { sort_perm(B, c, npc); });
     go = phase_done(F, PH_PERM, &sh);
@@ -2146,9 +2204,10 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_bricks(BatchDev B, uint32
 
 __global__ void __launch_bounds__(kSortThreads) k_sort_scan(BatchDev B, uint32_t bch)
 {
+    __shared__ Seg sv[kSortThreads];
     const uint32_t nb = (uint32_t)B.total_bricks;
     if (B.flags[BF_ANY_SORT])
-        scan_finish(B, blockIdx.x, min(blockIdx.x * bch, nb), min((blockIdx.x + 1) * bch, nb));
+        scan_finish(B, blockIdx.x, min(blockIdx.x * bch, nb), min((blockIdx.x + 1) * bch, nb), sv);
 }
 
 __global__ void __launch_bounds__(kSortThreads) k_sort_perm(BatchDev B)
@@ -2589,24 +2648,328 @@ __device__ inline bool same_base(const int a[3], const int b[3])
     return a[0] == b[0] && a[1] == b[1] && a[2] == b[2];
 }
 
+// LDS of a stress item: the nodal velocity tile, 12 bytes per node (FP32; x,
+// y in vxy, z in vz), and the force accumulators (GIMP: in the anchored layout
+// (12 x 9 x 9) when the item's node box fits it, else in the box's own layout).
+template <typename R, int SH>
+struct StressLds {
+    static constexpr int CAP = ShapeTraits<SH>::cap;
+    static constexpr int FCAP = SH == 1 ? kAnchCap : CAP;
+    R2<R> vxy[CAP];
+    R vz[CAP];
+    double f[3][FCAP];
+};
+
+// One item of the stress kernel over the node box t: nodal velocity, strain
+// increment, volume and stress update, nodal internal + external force.
+// Returns ERR_NONFINITE where a thread met a non-finite stress.
+template <typename R, int SH, int T, Nodes M>
+__device__ __attribute__((always_inline)) inline uint32_t
+stress_item(const SceneDev &S, const Item &item, const Parts<R> &P, const NodeBuf<R> &nb, const Tile &t,
+            const uint32_t (&pcell)[kChunk / T], R2<R> (&lvxy)[StressLds<R, SH>::CAP],
+            R (&lvz)[StressLds<R, SH>::CAP], double (&lf)[3][StressLds<R, SH>::FCAP])
+{
+    constexpr int NS = ShapeTraits<SH>::NS;
+    constexpr int KP = kChunk / T;
+    using C = Cache<SH, kStressCacheGather, kStressCacheScatter>;
+    constexpr bool GC = C::gather, SC = C::scatter;
+    constexpr int GN = C::gnodes, SN = C::snodes;
+    const int tv = t.dim[0] * t.dim[1] * t.dim[2];
+    // anchored GIMP scatter: every anchored node of the item's particles
+    // (cells lo..hi, nodes lo - 1 .. hi + 2) lies in the box, whose edges
+    // must fit the anchored layout
+    const bool anch = SH == 1 && t.dim[0] <= kAnchPX && t.dim[1] <= 9 && t.dim[2] <= 9;
+    auto fidx = [&](int q, int i, int j, int k) {
+        return anch ? (i - t.lo[0]) + kAnchPX * (j - t.lo[1]) + kAnchPXY * (k - t.lo[2]) : q;
+    };
+    for (int q = threadIdx.x; q < tv; q += blockDim.x) {
+        int i, j, k;
+        tile_node_small(t, q, i, j, k);
+        R v[3];
+        node_velocity<R, M>(S, nb, i, j, k, v);
+        lvxy[q] = R2<R>{v[0], v[1]};
+        lvz[q] = v[2];
+        const int fq = fidx(q, i, j, k);
+        lf[0][fq] = lf[1][fq] = lf[2][fq] = 0.0;
+    }
+    __syncthreads();
+    const R dt = cst<R>(S.dt, S.f_dt);
+    const R gx = cst<R>(S.g[0], S.f_g[0]), gy = cst<R>(S.g[1], S.f_g[1]), gz = cst<R>(S.g[2], S.f_g[2]);
+    uint32_t bad = 0;
+    int kb[3] = {-(1 << 30), 0, 0};   // support base held in the gather cache
+    int fb[3] = {-(1 << 30), 0, 0};   // support base of the force accumulators
+    Corners kc{};
+    R cv[GN][3], fa[SN][3];
+    auto flush = [&]() {
+        for (int n = 0; n < SN; ++n) {
+            const int li = kc.t0 + (n & 1) + ((n >> 1) & 1) * kc.ty + (n >> 2) * kc.tz;
+            for (int a = 0; a < 3; ++a)
+                atomicAdd(&lf[a][li], (double)fa[n][a]);
+        }
+    };
+#pragma unroll
+    for (int rr = 0; rr < KP; ++rr) {
+        const uint32_t q = threadIdx.x + rr * T;
+        if (q >= item.count)
+            break;
+        const uint32_t p = item.start + q;
+        const double xp[3] = {ldg(P.x[0], p), ldg(P.x[1], p), ldg(P.x[2], p)};
+        // every input of the particle in one round trip, except on
+        // isoparametric cells, whose inverse Jacobian leaves no registers
+        // for them (one wavefront per SIMD fewer, measured slower)
+        R vol0 = 0, sg[6] = {0, 0, 0, 0, 0, 0}, mp = 0;
+        if constexpr (SH != 2) {
+            vol0 = ldg(P.vol, p);
+            for (int k = 0; k < 6; ++k)
+                sg[k] = ldg(P.sig[k], p);
+            mp = ldg(P.mass, p);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // the particle's loads in one round trip
+        int c[3];
+        unpack_cell(pcell[rr], c);
+        Support<R, SH> sp;
+        make_support<R, SH>(S, xp, c, sp);
+        const Corners cn = corners(S, t, sp.base);
+        if constexpr (GC) {
+            if (!same_base(sp.base, kb)) {
+                for (int a = 0; a < 3; ++a)
+                    kb[a] = sp.base[a];
+                for (int n = 0; n < GN; ++n) {
+                    const int li = cn.t0 + (n & 1) + ((n >> 1) & 1) * cn.ty + (n >> 2) * cn.tz;
+                    const R2<R> v = lvxy[li];
+                    cv[n][0] = v.s;
+                    cv[n][1] = v.t;
+                    cv[n][2] = lvz[li];
+                }
+            }
+        }
+        if constexpr (SC) {
+            if (!same_base(sp.base, fb)) {
+                if (fb[0] != -(1 << 30))
+                    flush();
+                for (int a = 0; a < 3; ++a)
+                    fb[a] = sp.base[a];
+                kc = cn;
+                for (int n = 0; n < SN; ++n)
+                    fa[n][0] = fa[n][1] = fa[n][2] = (R)0;
+            }
+        }
+        R L[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        // linear shape functions: dN/dx_a is +-1/h times the product of the
+        // other two axes' weights (pair products below, shared with the
+        // force), so the gradient is a weighted sum of nodal differences
+        R Pyz[4], Pxz[4], Pxy[4];
+        if constexpr (SH != 1) {
+            for (int u = 0; u < 2; ++u)
+                for (int w = 0; w < 2; ++w) {
+                    Pyz[u + 2 * w] = sp.w[1][u] * sp.w[2][w];
+                    Pxz[u + 2 * w] = sp.w[0][u] * sp.w[2][w];
+                    Pxy[u + 2 * w] = sp.w[0][u] * sp.w[1][w];
+                }
+            R v8[8][3];
+            for (int n = 0; n < 8; ++n) {
+                if constexpr (GC) {
+                    v8[n][0] = cv[n][0];
+                    v8[n][1] = cv[n][1];
+                    v8[n][2] = cv[n][2];
+                } else {
+                    const int li = cn.t0 + (n & 1) + ((n >> 1) & 1) * cn.ty + (n >> 2) * cn.tz;
+                    const R2<R> w = lvxy[li];
+                    v8[n][0] = w.s;
+                    v8[n][1] = w.t;
+                    v8[n][2] = lvz[li];
+                }
+            }
+            const R ih = cst<R>(S.inv_h, S.f_inv_h);
+            for (int e = 0; e < 3; ++e) {
+                R gx = 0, gy = 0, gz = 0;
+                for (int u = 0; u < 2; ++u)
+                    for (int w = 0; w < 2; ++w) {
+                        gx += Pyz[u + 2 * w] * (v8[1 + 2 * u + 4 * w][e] - v8[2 * u + 4 * w][e]);
+                        gy += Pxz[u + 2 * w] * (v8[u + 2 + 4 * w][e] - v8[u + 4 * w][e]);
+                        gz += Pxy[u + 2 * w] * (v8[u + 2 * w + 4][e] - v8[u + 2 * w][e]);
+                    }
+                if constexpr (SH == 2) {   // d/dr to d/dx through (dx/dr)^-1
+                    for (int b = 0; b < 3; ++b)
+                        L[e][b] = gx * sp.Ji[0][b] + gy * sp.Ji[1][b] + gz * sp.Ji[2][b];
+                } else {
+                    L[e][0] = ih * gx;
+                    L[e][1] = ih * gy;
+                    L[e][2] = ih * gz;
+                }
+            }
+        } else {
+        // GIMP, row by row of the support: dN/dx = dw_i P1, dN/dy = w_i P2,
+        // dN/dz = w_i P3 with the row's (j, k) factors, so each row sums
+        // v dw_i and v w_i over i first
+        for (int k = 0; k < NS; ++k)
+            for (int j = 0; j < NS; ++j) {
+                const R P1 = sp.w[1][j] * sp.w[2][k], P2 = sp.dw[1][j] * sp.w[2][k],
+                        P3 = sp.w[1][j] * sp.dw[2][k];
+                R Sx[3] = {0, 0, 0}, Sw[3] = {0, 0, 0};
+                for (int i = 0; i < NS; ++i) {
+                    const int li = cn.t0 + i + j * cn.ty + k * cn.tz;
+                    const R2<R> w = lvxy[li];
+                    const R v[3] = {w.s, w.t, lvz[li]};
+                    for (int e = 0; e < 3; ++e) {
+                        Sx[e] += v[e] * sp.dw[0][i];
+                        Sw[e] += v[e] * sp.w[0][i];
+                    }
+                }
+                for (int e = 0; e < 3; ++e) {
+                    L[e][0] += Sx[e] * P1;
+                    L[e][1] += Sw[e] * P2;
+                    L[e][2] += Sw[e] * P3;
+                }
+                __builtin_amdgcn_sched_barrier(0);   // one support row of LDS reads in flight
+            }
+        }
+        const R de[6] = {dt * L[0][0], dt * L[1][1], dt * L[2][2], dt * (L[0][1] + L[1][0]),
+                         dt * (L[1][2] + L[2][1]), dt * (L[0][2] + L[2][0])};
+        if constexpr (SH == 2) {
+            vol0 = ldg(P.vol, p);
+            for (int k = 0; k < 6; ++k)
+                sg[k] = ldg(P.sig[k], p);
+        }
+        const R vol = vol0 * ((R)1 + de[0] + de[1] + de[2]);
+        constitutive<R>(S, de, sg);
+        for (int k = 0; k < 6; ++k) {
+            stg(P.sig[k], p, sg[k]);
+            if (!isfinite(sg[k]))
+                bad = ERR_NONFINITE;
+        }
+        stg(P.vol, p, vol);
+        if constexpr (SH == 2)
+            mp = ldg(P.mass, p);
+        auto deposit = [&](int i, int j, int k, R f0, R f1, R f2) {
+            if constexpr (SC) {
+                const int n = i + 2 * j + 4 * k;
+                fa[n][0] += f0;
+                fa[n][1] += f1;
+                fa[n][2] += f2;
+            } else {
+                const int li = cn.t0 + i + j * cn.ty + k * cn.tz;
+                atomicAdd(&lf[0][li], (double)f0);
+                atomicAdd(&lf[1][li], (double)f1);
+                atomicAdd(&lf[2][li], (double)f2);
+            }
+        };
+        if constexpr (SH != 1) {
+            // f_I = -V sigma . grad N_I + N_I m g with grad N_I = (1/h) (sx Pyz,
+            // sy Pxz, sz Pxy), s = -1 for the lower node of an axis; on an
+            // isoparametric cell grad N_I = Ji^T (sx Pyz, sy Pxz, sz Pxy), so
+            // f_Ia = sum_c B_ac dN_I/dr_c with B = -V sigma Ji^T
+            R B[3][3];
+            if constexpr (SH == 2) {
+                const R sm[3][3] = {{sg[0], sg[3], sg[5]}, {sg[3], sg[1], sg[4]}, {sg[5], sg[4], sg[2]}};
+                for (int a = 0; a < 3; ++a)
+                    for (int c2 = 0; c2 < 3; ++c2)
+                        B[a][c2] = -vol * (sm[a][0] * sp.Ji[c2][0] + sm[a][1] * sp.Ji[c2][1] +
+                                           sm[a][2] * sp.Ji[c2][2]);
+            } else {
+                const R c = -vol * cst<R>(S.inv_h, S.f_inv_h);
+                B[0][0] = c * sg[0];
+                B[1][1] = c * sg[1];
+                B[2][2] = c * sg[2];
+                B[0][1] = B[1][0] = c * sg[3];
+                B[1][2] = B[2][1] = c * sg[4];
+                B[0][2] = B[2][0] = c * sg[5];
+            }
+            const R mg0 = mp * gx, mg1 = mp * gy, mg2 = mp * gz;
+            for (int k = 0; k < 2; ++k)
+                for (int j = 0; j < 2; ++j)
+                    for (int i = 0; i < 2; ++i) {
+                        const R yz = Pyz[j + 2 * k], xz = Pxz[i + 2 * k], xy = Pxy[i + 2 * j];
+                        const R ax = i ? yz : -yz, ay = j ? xz : -xz, az = k ? xy : -xy;
+                        const R N = sp.w[0][i] * yz;
+                        deposit(i, j, k, N * mg0 + B[0][0] * ax + B[0][1] * ay + B[0][2] * az,
+                                N * mg1 + B[1][0] * ax + B[1][1] * ay + B[1][2] * az,
+                                N * mg2 + B[2][0] * ax + B[2][1] * ay + B[2][2] * az);
+                    }
+        } else if (anch) {
+            // the 27 support nodes in rotated order (see kAnchPX): on each
+            // axis slots 0 and 1 are the nodes c and c + 1, slot 2 the
+            // node c + 2 (support from c) or c - 1 (support from c - 1), so
+            // a wavefront's lanes mostly add to one translate of their
+            // cells.  f_a = A_a0 dN/dx + A_a1 dN/dy + A_a2 dN/dz + N m g_a
+            // with A = -V sigma, dN/dx = dw_i P1, dN/dy = w_i P2,
+            // dN/dz = w_i P3, N = w_i P1: the row's (j, k) factors once,
+            // then two terms per slot
+            R wr[3][3], dr[3][3];
+            int e[3];
+            for (int a = 0; a < 3; ++a)
+                e[a] = rotate3<R>(sp.w[a], sp.dw[a], sp.base[a] == c[a], wr[a], dr[a]);
+            R A[6];
+            for (int k = 0; k < 6; ++k)
+                A[k] = -vol * sg[k];
+            const R mg[3] = {mp * gx, mp * gy, mp * gz};
+            const int a0 = (c[0] - 1 - t.lo[0]) + kAnchPX * (c[1] - 1 - t.lo[1]) + kAnchPXY * (c[2] - 1 - t.lo[2]);
+            const int ox[3] = {1, 2, e[0]}, oy[3] = {kAnchPX, 2 * kAnchPX, kAnchPX * e[1]},
+                      oz[3] = {kAnchPXY, 2 * kAnchPXY, kAnchPXY * e[2]};
+            for (int k = 0; k < 3; ++k)
+                for (int j = 0; j < 3; ++j) {
+                    const R P1 = wr[1][j] * wr[2][k], P2 = dr[1][j] * wr[2][k], P3 = wr[1][j] * dr[2][k];
+                    const R X[3] = {A[0] * P1, A[3] * P1, A[5] * P1};
+                    const R Y[3] = {A[3] * P2 + A[5] * P3 + mg[0] * P1, A[1] * P2 + A[4] * P3 + mg[1] * P1,
+                                    A[4] * P2 + A[2] * P3 + mg[2] * P1};
+                    const int rb = a0 + oy[j] + oz[k];
+                    for (int i = 0; i < 3; ++i) {
+                        const int li = rb + ox[i];
+                        atomicAdd(&lf[0][li], (double)(dr[0][i] * X[0] + wr[0][i] * Y[0]));
+                        atomicAdd(&lf[1][li], (double)(dr[0][i] * X[1] + wr[0][i] * Y[1]));
+                        atomicAdd(&lf[2][li], (double)(dr[0][i] * X[2] + wr[0][i] * Y[2]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
+                }
+        } else {
+        for (int k = 0; k < NS; ++k)
+            for (int j = 0; j < NS; ++j)
+                for (int i = 0; i < NS; ++i) {
+                    const R wyz = sp.w[1][j] * sp.w[2][k];
+                    const R N = sp.w[0][i] * wyz;
+                    const R gxN = sp.dw[0][i] * wyz;
+                    const R gyN = sp.w[0][i] * sp.dw[1][j] * sp.w[2][k];
+                    const R gzN = sp.w[0][i] * sp.w[1][j] * sp.dw[2][k];
+                    const R f0 = -vol * (sg[0] * gxN + sg[3] * gyN + sg[5] * gzN) + N * mp * gx;
+                    const R f1 = -vol * (sg[3] * gxN + sg[1] * gyN + sg[4] * gzN) + N * mp * gy;
+                    const R f2 = -vol * (sg[5] * gxN + sg[4] * gyN + sg[2] * gzN) + N * mp * gz;
+                    deposit(i, j, k, f0, f1, f2);
+                    if constexpr (SH == 1)
+                        if (i == NS - 1)
+                            __builtin_amdgcn_sched_barrier(0);   // one support layer of LDS reads in flight
+                }
+        }
+    }
+    if constexpr (SC)
+        if (fb[0] != -(1 << 30))
+            flush();
+    __syncthreads();
+    for (int q = threadIdx.x; q < tv; q += blockDim.x) {
+        int i, j, k;
+        tile_node_small(t, q, i, j, k);
+        const int fq = fidx(q, i, j, k);
+        const R f0 = (R)lf[0][fq], f1 = (R)lf[1][fq], f2 = (R)lf[2][fq];
+        if (f0 == (R)0 && f1 == (R)0 && f2 == (R)0)
+            continue;
+        const uint32_t I = node_id(S, i, j, k);
+        addg(nb.f[0], I, f0);
+        addg(nb.f[1], I, f1);
+        addg(nb.f[2], I, f2);
+    }
+    __syncthreads();
+    return bad;
+}
+
 // USF: zero the previous step's node buffer; nodal velocity, strain
 // increment, volume and stress update, nodal internal + external force.
 template <typename R, int SH, int T>
 __global__ void __launch_bounds__(T) k_stress(BatchDev B)
 {
-    constexpr int NS = ShapeTraits<SH>::NS;
-    constexpr int CAP = ShapeTraits<SH>::cap;
     constexpr int KP = kChunk / T;
-    using C = Cache<SH, kStressCacheGather, kStressCacheScatter>;
-    constexpr bool GC = C::gather, SC = C::scatter;
-    constexpr int GN = C::gnodes, SN = C::snodes;
-    // GIMP force accumulators in the anchored layout (12 x 9 x 9) when the
-    // item's node box fits it, else in the box's own layout
-    constexpr int FCAP = SH == 1 ? kAnchCap : CAP;
-    // nodal velocity tile, 12 bytes per node (FP32): x, y in lvxy, z in lvz
-    __shared__ R2<R> lvxy[CAP];
-    __shared__ R lvz[CAP];
-    __shared__ double lf[3][FCAP];
+    using L = StressLds<R, SH>;
+    __shared__ R2<R> lvxy[L::CAP];
+    __shared__ R lvz[L::CAP];
+    __shared__ double lf[3][L::FCAP];
     __shared__ int red[6 * (T / 64)];
     clear_reorder_flags(B);
     clear_previous<R>(B);
@@ -2655,291 +3018,9 @@ __global__ void __launch_bounds__(T) k_stress(BatchDev B)
             __syncthreads();
             continue;
         }
-        const int tv = t.dim[0] * t.dim[1] * t.dim[2];
-        // anchored GIMP scatter: every anchored node of the item's particles
-        // (cells lo..hi, nodes lo - 1 .. hi + 2) lies in the box, whose edges
-        // must fit the anchored layout
-        const bool anch = SH == 1 && t.dim[0] <= kAnchPX && t.dim[1] <= 9 && t.dim[2] <= 9;
-        auto fidx = [&](int q, int i, int j, int k) {
-            return anch ? (i - t.lo[0]) + kAnchPX * (j - t.lo[1]) + kAnchPXY * (k - t.lo[2]) : q;
-        };
-        for (int q = threadIdx.x; q < tv; q += blockDim.x) {
-            int i, j, k;
-            tile_node_small(t, q, i, j, k);
-            R v[3];
-            node_velocity<R>(S, nb, i, j, k, v);
-            lvxy[q] = R2<R>{v[0], v[1]};
-            lvz[q] = v[2];
-            const int fq = fidx(q, i, j, k);
-            lf[0][fq] = lf[1][fq] = lf[2][fq] = 0.0;
-        }
-        __syncthreads();
-        const R dt = cst<R>(S.dt, S.f_dt);
-        const R gx = cst<R>(S.g[0], S.f_g[0]), gy = cst<R>(S.g[1], S.f_g[1]), gz = cst<R>(S.g[2], S.f_g[2]);
-        uint32_t bad = 0;
-        int kb[3] = {-(1 << 30), 0, 0};   // support base held in the gather cache
-        int fb[3] = {-(1 << 30), 0, 0};   // support base of the force accumulators
-        Corners kc{};
-        R cv[GN][3], fa[SN][3];
-        auto flush = [&]() {
-            for (int n = 0; n < SN; ++n) {
-                const int li = kc.t0 + (n & 1) + ((n >> 1) & 1) * kc.ty + (n >> 2) * kc.tz;
-                for (int a = 0; a < 3; ++a)
-                    atomicAdd(&lf[a][li], (double)fa[n][a]);
-            }
-        };
-#pragma unroll
-        for (int rr = 0; rr < KP; ++rr) {
-            const uint32_t q = threadIdx.x + rr * T;
-            if (q >= item.count)
-                break;
-            const uint32_t p = item.start + q;
-            const double xp[3] = {ldg(P.x[0], p), ldg(P.x[1], p), ldg(P.x[2], p)};
-            // every input of the particle in one round trip, except on
-            // isoparametric cells, whose inverse Jacobian leaves no registers
-            // for them (one wavefront per SIMD fewer, measured slower)
-            R vol0 = 0, sg[6] = {0, 0, 0, 0, 0, 0}, mp = 0;
-            if constexpr (SH != 2) {
-                vol0 = ldg(P.vol, p);
-                for (int k = 0; k < 6; ++k)
-                    sg[k] = ldg(P.sig[k], p);
-                mp = ldg(P.mass, p);
-            }
-            __builtin_amdgcn_sched_barrier(0);   // the particle's loads in one round trip
-            int c[3];
-            unpack_cell(pcell[rr], c);
-            Support<R, SH> sp;
-            make_support<R, SH>(S, xp, c, sp);
-            const Corners cn = corners(S, t, sp.base);
-            if constexpr (GC) {
-                if (!same_base(sp.base, kb)) {
-                    for (int a = 0; a < 3; ++a)
-                        kb[a] = sp.base[a];
-                    for (int n = 0; n < GN; ++n) {
-                        const int li = cn.t0 + (n & 1) + ((n >> 1) & 1) * cn.ty + (n >> 2) * cn.tz;
-                        const R2<R> v = lvxy[li];
-                        cv[n][0] = v.s;
-                        cv[n][1] = v.t;
-                        cv[n][2] = lvz[li];
-                    }
-                }
-            }
-            if constexpr (SC) {
-                if (!same_base(sp.base, fb)) {
-                    if (fb[0] != -(1 << 30))
-                        flush();
-                    for (int a = 0; a < 3; ++a)
-                        fb[a] = sp.base[a];
-                    kc = cn;
-                    for (int n = 0; n < SN; ++n)
-                        fa[n][0] = fa[n][1] = fa[n][2] = (R)0;
-                }
-            }
-            R L[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-            // linear shape functions: dN/dx_a is +-1/h times the product of the
-            // other two axes' weights (pair products below, shared with the
-            // force), so the gradient is a weighted sum of nodal differences
-            R Pyz[4], Pxz[4], Pxy[4];
-            if constexpr (SH != 1) {
-                for (int u = 0; u < 2; ++u)
-                    for (int w = 0; w < 2; ++w) {
-                        Pyz[u + 2 * w] = sp.w[1][u] * sp.w[2][w];
-                        Pxz[u + 2 * w] = sp.w[0][u] * sp.w[2][w];
-                        Pxy[u + 2 * w] = sp.w[0][u] * sp.w[1][w];
-                    }
-                R v8[8][3];
-                for (int n = 0; n < 8; ++n) {
-                    if constexpr (GC) {
-                        v8[n][0] = cv[n][0];
-                        v8[n][1] = cv[n][1];
-                        v8[n][2] = cv[n][2];
-                    } else {
-                        const int li = cn.t0 + (n & 1) + ((n >> 1) & 1) * cn.ty + (n >> 2) * cn.tz;
-                        const R2<R> w = lvxy[li];
-                        v8[n][0] = w.s;
-                        v8[n][1] = w.t;
-                        v8[n][2] = lvz[li];
-                    }
-                }
-                const R ih = cst<R>(S.inv_h, S.f_inv_h);
-                for (int e = 0; e < 3; ++e) {
-                    R gx = 0, gy = 0, gz = 0;
-                    for (int u = 0; u < 2; ++u)
-                        for (int w = 0; w < 2; ++w) {
-                            gx += Pyz[u + 2 * w] * (v8[1 + 2 * u + 4 * w][e] - v8[2 * u + 4 * w][e]);
-                            gy += Pxz[u + 2 * w] * (v8[u + 2 + 4 * w][e] - v8[u + 4 * w][e]);
-                            gz += Pxy[u + 2 * w] * (v8[u + 2 * w + 4][e] - v8[u + 2 * w][e]);
-                        }
-                    if constexpr (SH == 2) {   // d/dr to d/dx through (dx/dr)^-1
-                        for (int b = 0; b < 3; ++b)
-                            L[e][b] = gx * sp.Ji[0][b] + gy * sp.Ji[1][b] + gz * sp.Ji[2][b];
-                    } else {
-                        L[e][0] = ih * gx;
-                        L[e][1] = ih * gy;
-                        L[e][2] = ih * gz;
-                    }
-                }
-            } else {
-            // GIMP, row by row of the support: dN/dx = dw_i P1, dN/dy = w_i P2,
-            // dN/dz = w_i P3 with the row's (j, k) factors, so each row sums
-            // v dw_i and v w_i over i first
-            for (int k = 0; k < NS; ++k)
-                for (int j = 0; j < NS; ++j) {
-                    const R P1 = sp.w[1][j] * sp.w[2][k], P2 = sp.dw[1][j] * sp.w[2][k],
-                            P3 = sp.w[1][j] * sp.dw[2][k];
-                    R Sx[3] = {0, 0, 0}, Sw[3] = {0, 0, 0};
-                    for (int i = 0; i < NS; ++i) {
-                        const int li = cn.t0 + i + j * cn.ty + k * cn.tz;
-                        const R2<R> w = lvxy[li];
-                        const R v[3] = {w.s, w.t, lvz[li]};
-                        for (int e = 0; e < 3; ++e) {
-                            Sx[e] += v[e] * sp.dw[0][i];
-                            Sw[e] += v[e] * sp.w[0][i];
-                        }
-                    }
-                    for (int e = 0; e < 3; ++e) {
-                        L[e][0] += Sx[e] * P1;
-                        L[e][1] += Sw[e] * P2;
-                        L[e][2] += Sw[e] * P3;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // one support row of LDS reads in flight
-                }
-            }
-            const R de[6] = {dt * L[0][0], dt * L[1][1], dt * L[2][2], dt * (L[0][1] + L[1][0]),
-                             dt * (L[1][2] + L[2][1]), dt * (L[0][2] + L[2][0])};
-            if constexpr (SH == 2) {
-                vol0 = ldg(P.vol, p);
-                for (int k = 0; k < 6; ++k)
-                    sg[k] = ldg(P.sig[k], p);
-            }
-            const R vol = vol0 * ((R)1 + de[0] + de[1] + de[2]);
-            constitutive<R>(S, de, sg);
-            for (int k = 0; k < 6; ++k) {
-                stg(P.sig[k], p, sg[k]);
-                if (!isfinite(sg[k]))
-                    bad = ERR_NONFINITE;
-            }
-            stg(P.vol, p, vol);
-            if constexpr (SH == 2)
-                mp = ldg(P.mass, p);
-            auto deposit = [&](int i, int j, int k, R f0, R f1, R f2) {
-                if constexpr (SC) {
-                    const int n = i + 2 * j + 4 * k;
-                    fa[n][0] += f0;
-                    fa[n][1] += f1;
-                    fa[n][2] += f2;
-                } else {
-                    const int li = cn.t0 + i + j * cn.ty + k * cn.tz;
-                    atomicAdd(&lf[0][li], (double)f0);
-                    atomicAdd(&lf[1][li], (double)f1);
-                    atomicAdd(&lf[2][li], (double)f2);
-                }
-            };
-            if constexpr (SH != 1) {
-                // f_I = -V sigma . grad N_I + N_I m g with grad N_I = (1/h) (sx Pyz,
-                // sy Pxz, sz Pxy), s = -1 for the lower node of an axis; on an
-                // isoparametric cell grad N_I = Ji^T (sx Pyz, sy Pxz, sz Pxy), so
-                // f_Ia = sum_c B_ac dN_I/dr_c with B = -V sigma Ji^T
-                R B[3][3];
-                if constexpr (SH == 2) {
-                    const R sm[3][3] = {{sg[0], sg[3], sg[5]}, {sg[3], sg[1], sg[4]}, {sg[5], sg[4], sg[2]}};
-                    for (int a = 0; a < 3; ++a)
-                        for (int c2 = 0; c2 < 3; ++c2)
-                            B[a][c2] = -vol * (sm[a][0] * sp.Ji[c2][0] + sm[a][1] * sp.Ji[c2][1] +
-                                               sm[a][2] * sp.Ji[c2][2]);
-                } else {
-                    const R c = -vol * cst<R>(S.inv_h, S.f_inv_h);
-                    B[0][0] = c * sg[0];
-                    B[1][1] = c * sg[1];
-                    B[2][2] = c * sg[2];
-                    B[0][1] = B[1][0] = c * sg[3];
-                    B[1][2] = B[2][1] = c * sg[4];
-                    B[0][2] = B[2][0] = c * sg[5];
-                }
-                const R mg0 = mp * gx, mg1 = mp * gy, mg2 = mp * gz;
-                for (int k = 0; k < 2; ++k)
-                    for (int j = 0; j < 2; ++j)
-                        for (int i = 0; i < 2; ++i) {
-                            const R yz = Pyz[j + 2 * k], xz = Pxz[i + 2 * k], xy = Pxy[i + 2 * j];
-                            const R ax = i ? yz : -yz, ay = j ? xz : -xz, az = k ? xy : -xy;
-                            const R N = sp.w[0][i] * yz;
-                            deposit(i, j, k, N * mg0 + B[0][0] * ax + B[0][1] * ay + B[0][2] * az,
-                                    N * mg1 + B[1][0] * ax + B[1][1] * ay + B[1][2] * az,
-                                    N * mg2 + B[2][0] * ax + B[2][1] * ay + B[2][2] * az);
-                        }
-            } else if (anch) {
-                // the 27 support nodes in rotated order (see kAnchPX): on each
-                // axis slots 0 and 1 are the nodes c and c + 1, slot 2 the
-                // node c + 2 (support from c) or c - 1 (support from c - 1), so
-                // a wavefront's lanes mostly add to one translate of their
-                // cells.  f_a = A_a0 dN/dx + A_a1 dN/dy + A_a2 dN/dz + N m g_a
-                // with A = -V sigma, dN/dx = dw_i P1, dN/dy = w_i P2,
-                // dN/dz = w_i P3, N = w_i P1: the row's (j, k) factors once,
-                // then two terms per slot
-                R wr[3][3], dr[3][3];
-                int e[3];
-                for (int a = 0; a < 3; ++a)
-                    e[a] = rotate3<R>(sp.w[a], sp.dw[a], sp.base[a] == c[a], wr[a], dr[a]);
-                R A[6];
-                for (int k = 0; k < 6; ++k)
-                    A[k] = -vol * sg[k];
-                const R mg[3] = {mp * gx, mp * gy, mp * gz};
-                const int a0 = (c[0] - 1 - t.lo[0]) + kAnchPX * (c[1] - 1 - t.lo[1]) + kAnchPXY * (c[2] - 1 - t.lo[2]);
-                const int ox[3] = {1, 2, e[0]}, oy[3] = {kAnchPX, 2 * kAnchPX, kAnchPX * e[1]},
-                          oz[3] = {kAnchPXY, 2 * kAnchPXY, kAnchPXY * e[2]};
-                for (int k = 0; k < 3; ++k)
-                    for (int j = 0; j < 3; ++j) {
-                        const R P1 = wr[1][j] * wr[2][k], P2 = dr[1][j] * wr[2][k], P3 = wr[1][j] * dr[2][k];
-                        const R X[3] = {A[0] * P1, A[3] * P1, A[5] * P1};
-                        const R Y[3] = {A[3] * P2 + A[5] * P3 + mg[0] * P1, A[1] * P2 + A[4] * P3 + mg[1] * P1,
-                                        A[4] * P2 + A[2] * P3 + mg[2] * P1};
-                        const int rb = a0 + oy[j] + oz[k];
-                        for (int i = 0; i < 3; ++i) {
-                            const int li = rb + ox[i];
-                            atomicAdd(&lf[0][li], (double)(dr[0][i] * X[0] + wr[0][i] * Y[0]));
-                            atomicAdd(&lf[1][li], (double)(dr[0][i] * X[1] + wr[0][i] * Y[1]));
-                            atomicAdd(&lf[2][li], (double)(dr[0][i] * X[2] + wr[0][i] * Y[2]));
-                        }
-                        __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
-                    }
-            } else {
-            for (int k = 0; k < NS; ++k)
-                for (int j = 0; j < NS; ++j)
-                    for (int i = 0; i < NS; ++i) {
-                        const R wyz = sp.w[1][j] * sp.w[2][k];
-                        const R N = sp.w[0][i] * wyz;
-                        const R gxN = sp.dw[0][i] * wyz;
-                        const R gyN = sp.w[0][i] * sp.dw[1][j] * sp.w[2][k];
-                        const R gzN = sp.w[0][i] * sp.w[1][j] * sp.dw[2][k];
-                        const R f0 = -vol * (sg[0] * gxN + sg[3] * gyN + sg[5] * gzN) + N * mp * gx;
-                        const R f1 = -vol * (sg[3] * gxN + sg[1] * gyN + sg[4] * gzN) + N * mp * gy;
-                        const R f2 = -vol * (sg[5] * gxN + sg[4] * gyN + sg[2] * gzN) + N * mp * gz;
-                        deposit(i, j, k, f0, f1, f2);
-                        if constexpr (SH == 1)
-                            if (i == NS - 1)
-                                __builtin_amdgcn_sched_barrier(0);   // one support layer of LDS reads in flight
-                    }
-            }
-        }
-        if constexpr (SC)
-            if (fb[0] != -(1 << 30))
-                flush();
+        const uint32_t bad = stress_item<R, SH, T, PLAIN>(S, item, P, nb, t, pcell, lvxy, lvz, lf);
         if (bad)
             atomicOr(&S.ctl[CTL_ERR], bad);
-        __syncthreads();
-        for (int q = threadIdx.x; q < tv; q += blockDim.x) {
-            int i, j, k;
-            tile_node_small(t, q, i, j, k);
-            const int fq = fidx(q, i, j, k);
-            const R f0 = (R)lf[0][fq], f1 = (R)lf[1][fq], f2 = (R)lf[2][fq];
-            if (f0 == (R)0 && f1 == (R)0 && f2 == (R)0)
-                continue;
-            const uint32_t I = node_id(S, i, j, k);
-            addg(nb.f[0], I, f0);
-            addg(nb.f[1], I, f1);
-            addg(nb.f[2], I, f2);
-        }
-        __syncthreads();
     }
 }
 
@@ -2961,19 +3042,407 @@ __device__ inline void load_update_tile(const SceneDev &S, const NodeBuf<R> &nb,
 
 // Load the acceleration and updated velocity of the item's node tile into
 // 24 bytes per node (FP32): a and vn.x in la, vn.y and vn.z in lyz.
-template <typename R>
+template <typename R, Nodes M = PLAIN>
 __device__ inline void load_update_tile_packed(const SceneDev &S, const NodeBuf<R> &nb, const Tile &t, R4<R> *la,
-                                               R2<R> *lyz)
+                                               R2<R> *lyz, int64_t step = -1)
 {
     const int tv = t.dim[0] * t.dim[1] * t.dim[2];
     for (int q = threadIdx.x; q < tv; q += blockDim.x) {
         int i, j, k;
         tile_node_small(t, q, i, j, k);
         R a[3], vn[3];
-        node_update<R>(S, nb, i, j, k, a, vn);
+        node_update<R, M>(S, nb, i, j, k, a, vn, step);
         la[q] = R4<R>{a[0], a[1], a[2], vn[0]};
         lyz[q] = R2<R>{vn[1], vn[2]};
     }
+}
+
+// LDS of a G2P+P2G item: the gather tile, 24 bytes per node (FP32; an
+// acceleration and updated velocity packed, which leaves room for one more
+// workgroup per CU), and the home-tile accumulators, edge HD, at row and
+// plane pitches APX, APXY (GIMP: the anchored layout, see kAnchPX).  GIMP: the
+// two share LDS (all particles are updated before the scatter starts), which
+// admits one more workgroup per CU.
+template <typename R, int SH>
+struct G2pLds {
+    static constexpr int CAP = ShapeTraits<SH>::cap;
+    static constexpr bool OVERLAY = SH == 1;
+    static constexpr int HD = kBrick + 2 + ShapeTraits<SH>::lo + ShapeTraits<SH>::hi;   // home tile edge
+    static constexpr int APX = SH == 1 ? kAnchPX : HD, APXY = SH == 1 ? kAnchPXY : HD * HD;
+    static constexpr int ACAP = APXY * HD;
+    static_assert(SH != 1 || (HD == 9 && ACAP == kAnchCap), "anchored layout holds the GIMP home tile");
+    static constexpr int TILE_BYTES = CAP * (int)(sizeof(R4<R>) + sizeof(R2<R>));
+    static constexpr int ACC_BYTES = 4 * ACAP * (int)sizeof(double);
+    static_assert((CAP * sizeof(R4<R>)) % alignof(R2<R>) == 0 && TILE_BYTES % alignof(double) == 0, "tile alignment");
+    static constexpr int BYTES =
+        OVERLAY ? (TILE_BYTES > ACC_BYTES ? TILE_BYTES : ACC_BYTES) : TILE_BYTES + ACC_BYTES;
+    __attribute__((aligned(16))) char raw[BYTES];
+    __device__ R4<R> *la() { return (R4<R> *)raw; }
+    __device__ R2<R> *lyz() { return (R2<R> *)(raw + CAP * sizeof(R4<R>)); }
+    __device__ double (*acc())[ACAP] { return (double (*)[ACAP])(raw + (OVERLAY ? 0 : TILE_BYTES)); }
+};
+
+// What an item's particle moves report: error bits, particles outside the
+// mesh, whether one left its home region (per thread), and the node box of the
+// moved particles (the item's).
+struct Moves {
+    uint32_t err, lost, drift;
+    Tile box;
+};
+
+// One item of the G2P+P2G kernel: the step's node buffer nb over the box t,
+// the next step's nn.  Without OVERLAY the accumulators are zero on entry and
+// are left so.  step: see external_force_scale().
+template <typename R, int SH, int T, Nodes M>
+__device__ __attribute__((always_inline)) inline Moves g2p_item(const SceneDev &S, const Item &item, const Parts<R> &P,
+                                                                const NodeBuf<R> &nb, const NodeBuf<R> &nn,
+                                                                const Tile &t, G2pLds<R, SH> &lds, int *red,
+                                                                int64_t step)
+{
+    using L = G2pLds<R, SH>;
+    constexpr int NS = ShapeTraits<SH>::NS;
+    constexpr int KP = kChunk / T;
+    using C = Cache<SH, kG2PCacheGather, kG2PCacheScatter>;
+    constexpr bool GC = C::gather, SC = C::scatter;
+    constexpr int GN = C::gnodes, SN = C::snodes;
+    constexpr bool OVERLAY = L::OVERLAY;
+    constexpr int HD = L::HD, APX = L::APX, APXY = L::APXY, ACAP = L::ACAP;
+    R4<R> *la = lds.la();
+    R2<R> *lyz = lds.lyz();
+    double (*acc)[ACAP] = lds.acc();
+    int o[3];
+    brick_origin(S, item.brick, o);
+    const Tile ht = home_tile<SH>(o);
+    load_update_tile_packed<R, M>(S, nb, t, la, lyz, step);
+    __syncthreads();
+    const R dt = cst<R>(S.dt, S.f_dt);
+    const int pic = S.vel_update == 1;
+    uint32_t err = 0, drift = 0, lost = 0;
+    int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
+    // gather cache (old support) and scatter cache (new support)
+    int gb[3] = {-(1 << 30), 0, 0}, sb[3] = {-(1 << 30), 0, 0};
+    R ca[GN][3], cu[GN][3], sp_[SN][3], sm[SN];
+    Corners sc{};
+    bool s_in = true;
+    // the moved particles awaiting the scatter (OVERLAY)
+    struct Moved {
+        double x[3];
+        R m, mv[3];
+        int c[3];
+        bool ok, in;
+    };
+    Moved mvd[OVERLAY ? KP : 1];
+    if constexpr (OVERLAY)
+        for (int rr = 0; rr < KP; ++rr)
+            mvd[rr].ok = false;
+    // next step's mass and momentum of one particle with support sp:
+    // into the home tile's accumulators, or (drifted) global memory
+    auto scatter = [&](const Support<R, SH> &sq, const int cq[3], bool inh, R m, const R mvq[3]) {
+        const Corners hq = corners(S, ht, sq.base);
+        if (SH == 1 && inh) {
+            // anchored 4 x 4 x 4 slots (see kAnchPX); home-tile coordinates
+            // of node c - 1 are c - o + 1 in [0, 5] for a cell in the home region
+            R w4[3][4], dw4[3][4];
+            for (int a = 0; a < 3; ++a)
+                anchor4<R>(sq.w[a], sq.dw[a], sq.base[a] == cq[a] ? 1 : 0, w4[a], dw4[a]);
+            const int a0 = (cq[0] - 1 - ht.lo[0]) + APX * (cq[1] - 1 - ht.lo[1]) + APXY * (cq[2] - 1 - ht.lo[2]);
+            for (int k = 0; k < 4; ++k)
+                for (int j = 0; j < 4; ++j) {
+                    const R wyz = w4[1][j] * w4[2][k];
+                    for (int i = 0; i < 4; ++i) {
+                        const R N = w4[0][i] * wyz;
+                        const int li = a0 + i + APX * j + APXY * k;
+                        atomicAdd(&acc[0][li], (double)(N * m));
+                        atomicAdd(&acc[1][li], (double)(N * mvq[0]));
+                        atomicAdd(&acc[2][li], (double)(N * mvq[1]));
+                        atomicAdd(&acc[3][li], (double)(N * mvq[2]));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
+                }
+        } else if (inh) {
+            for (int k = 0; k < NS; ++k)
+                for (int j = 0; j < NS; ++j)
+                    for (int i = 0; i < NS; ++i) {
+                        const R N = sq.w[0][i] * sq.w[1][j] * sq.w[2][k];
+                        const int li = hq.t0 + i + j * hq.ty + k * hq.tz;
+                        atomicAdd(&acc[0][li], (double)(N * m));
+                        atomicAdd(&acc[1][li], (double)(N * mvq[0]));
+                        atomicAdd(&acc[2][li], (double)(N * mvq[1]));
+                        atomicAdd(&acc[3][li], (double)(N * mvq[2]));
+                    }
+        } else {
+            for (int k = 0; k < NS; ++k)
+                for (int j = 0; j < NS; ++j)
+                    for (int i = 0; i < NS; ++i) {
+                        const R N = sq.w[0][i] * sq.w[1][j] * sq.w[2][k];
+                        const uint32_t I = hq.n0 + (uint32_t)(i + j * hq.ny + k * hq.nz);
+                        addg(nn.m, I, (double)(N * m));
+                        for (int a = 0; a < 3; ++a)
+                            addg(nn.p[a], I, N * mvq[a]);
+                    }
+        }
+    };
+    // two particles in one home cell (GIMP): one set of anchored adds
+    // carries the sum of their contributions
+    auto scatter_pair = [&](const Support<R, SH> &sa, const Support<R, SH> &sb, const int cq[3], R ma,
+                            const R mva[3], R mb, const R mvb[3]) {
+        R wa[3][4], wb[3][4], unused[4];
+        for (int a = 0; a < 3; ++a) {
+            anchor4<R>(sa.w[a], sa.dw[a], sa.base[a] == cq[a] ? 1 : 0, wa[a], unused);
+            anchor4<R>(sb.w[a], sb.dw[a], sb.base[a] == cq[a] ? 1 : 0, wb[a], unused);
+        }
+        const int a0 = (cq[0] - 1 - ht.lo[0]) + APX * (cq[1] - 1 - ht.lo[1]) + APXY * (cq[2] - 1 - ht.lo[2]);
+        for (int k = 0; k < 4; ++k)
+            for (int j = 0; j < 4; ++j) {
+                const R ya = wa[1][j] * wa[2][k], yb = wb[1][j] * wb[2][k];
+                for (int i = 0; i < 4; ++i) {
+                    const R Na = wa[0][i] * ya, Nb = wb[0][i] * yb;
+                    const int li = a0 + i + APX * j + APXY * k;
+                    atomicAdd(&acc[0][li], (double)(Na * ma + Nb * mb));
+                    atomicAdd(&acc[1][li], (double)(Na * mva[0] + Nb * mvb[0]));
+                    atomicAdd(&acc[2][li], (double)(Na * mva[1] + Nb * mvb[1]));
+                    atomicAdd(&acc[3][li], (double)(Na * mva[2] + Nb * mvb[2]));
+                }
+                __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
+            }
+    };
+    auto flush = [&]() {
+        for (int n = 0; n < SN; ++n) {
+            const int di = n & 1, dj = (n >> 1) & 1, dk = n >> 2;
+            if (s_in) {
+                const int li = sc.t0 + di + dj * sc.ty + dk * sc.tz;
+                atomicAdd(&acc[0][li], (double)sm[n]);
+                for (int a = 0; a < 3; ++a)
+                    atomicAdd(&acc[1 + a][li], (double)sp_[n][a]);
+            } else {
+                const uint32_t I = sc.n0 + (uint32_t)(di + dj * sc.ny + dk * sc.nz);
+                addg(nn.m, I, (double)sm[n]);
+                for (int a = 0; a < 3; ++a)
+                    addg(nn.p[a], I, sp_[n][a]);
+            }
+        }
+    };
+#pragma unroll
+    for (int rr = 0; rr < KP; ++rr) {
+        const uint32_t q = threadIdx.x + rr * T;
+        if (q >= item.count)
+            break;
+        const uint32_t p = item.start + q;
+        double xp[3] = {ldg(P.x[0], p), ldg(P.x[1], p), ldg(P.x[2], p)};
+        const R pv[3] = {ldg(P.v[0], p), ldg(P.v[1], p), ldg(P.v[2], p)};
+        const R mp = ldg(P.mass, p);
+        const uint32_t pc = ldg(P.cell, p);
+        __builtin_amdgcn_sched_barrier(0);   // the particle's loads in one round trip
+        int c[3];
+        unpack_cell(pc, c);
+        Support<R, SH> sp;
+        IsoAt iso;
+        if constexpr (SH == 2)
+            iso_at<R>(S, xp, c, sp, iso);
+        else
+            make_support<R, SH>(S, xp, c, sp);
+        pin_loaded(pv);
+        const Corners cn = corners(S, t, sp.base);
+        if constexpr (GC) {
+            if (!same_base(sp.base, gb)) {
+                for (int a = 0; a < 3; ++a)
+                    gb[a] = sp.base[a];
+                for (int n = 0; n < GN; ++n) {
+                    const int li = cn.t0 + (n & 1) + ((n >> 1) & 1) * cn.ty + (n >> 2) * cn.tz;
+                    const R4<R> a4 = la[li];
+                    const R2<R> u2 = lyz[li];
+                    ca[n][0] = a4.x;
+                    ca[n][1] = a4.y;
+                    ca[n][2] = a4.z;
+                    cu[n][0] = a4.w;
+                    cu[n][1] = u2.s;
+                    cu[n][2] = u2.t;
+                }
+            }
+        }
+        R dv[3] = {0, 0, 0}, vp[3] = {0, 0, 0};
+        for (int k = 0; k < NS; ++k)
+            for (int j = 0; j < NS; ++j)
+                for (int i = 0; i < NS; ++i) {
+                    const R N = sp.w[0][i] * sp.w[1][j] * sp.w[2][k];
+                    R a[3], u[3];
+                    if constexpr (GC) {
+                        const int n = i + 2 * j + 4 * k;
+                        for (int e = 0; e < 3; ++e) {
+                            a[e] = ca[n][e];
+                            u[e] = cu[n][e];
+                        }
+                    } else {
+                        const int li = cn.t0 + i + j * cn.ty + k * cn.tz;
+                        const R4<R> a4 = la[li];
+                        const R2<R> u2 = lyz[li];
+                        a[0] = a4.x;
+                        a[1] = a4.y;
+                        a[2] = a4.z;
+                        u[0] = a4.w;
+                        u[1] = u2.s;
+                        u[2] = u2.t;
+                    }
+                    for (int e = 0; e < 3; ++e) {
+                        dv[e] += N * a[e];
+                        vp[e] += N * u[e];
+                    }
+                    if constexpr (SH == 1)
+                        if (i == NS - 1)
+                            __builtin_amdgcn_sched_barrier(0);   // one support layer of LDS reads in flight
+                }
+        R nv[3];
+        double dx[3];
+        for (int a = 0; a < 3; ++a) {
+            nv[a] = pic ? vp[a] : pv[a] + dt * dv[a];
+            stg(P.v[a], p, nv[a]);
+            dx[a] = S.dt * (double)vp[a];
+            xp[a] += dx[a];
+            stg(P.x[a], p, xp[a]);
+            if (!isfinite(nv[a]))
+                err |= ERR_NONFINITE;
+        }
+        int nc[3];
+        double fr[3];
+        uint32_t e;
+        if constexpr (SH == 2) {   // walk from the old cell; fr: local coordinates in the new one
+            for (int a = 0; a < 3; ++a)
+                nc[a] = c[a];
+            e = iso_moved(S, xp, dx, nc, iso);
+            for (int a = 0; a < 3; ++a)
+                fr[a] = iso.r[a];
+        } else {
+            e = locate<SH == 0>(S, xp, nc, fr);
+        }
+        if (e) {
+            err |= e;   // keep the old cell; the scene stops after this step
+            lost += (e & ERR_OUT_OF_MESH) ? 1u : 0u;
+            continue;
+        }
+        stg(P.cell, p, pack_cell(nc));
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = min(mn[a], nc[a]);
+            mx[a] = max(mx[a], nc[a]);
+        }
+        const bool in = in_home(nc, o);
+        drift |= in ? 0u : 1u;
+        if constexpr (OVERLAY) {
+            Moved &mq = mvd[rr];
+            for (int a = 0; a < 3; ++a) {
+                mq.x[a] = xp[a];
+                mq.c[a] = nc[a];
+                mq.mv[a] = mp * nv[a];
+            }
+            mq.m = mp;
+            mq.in = in;
+            mq.ok = true;
+            continue;
+        }
+        // the next step's P2G from the updated particle (trilinear: the
+        // local coordinate is the cell search's fractional part, or the
+        // isoparametric walk's local coordinates)
+        if constexpr (SH != 1) {
+            const R ih = cst<R>(S.inv_h, S.f_inv_h);
+            for (int a = 0; a < 3; ++a) {
+                const R r = (R)fr[a];
+                sp.base[a] = nc[a];
+                sp.w[a][0] = (R)1 - r;
+                sp.w[a][1] = r;
+                sp.dw[a][0] = -ih;
+                sp.dw[a][1] = ih;
+            }
+        } else {
+            make_support<R, SH>(S, xp, nc, sp);
+        }
+        const Corners hn = corners(S, ht, sp.base);
+        const R mv[3] = {mp * nv[0], mp * nv[1], mp * nv[2]};
+        if constexpr (SC) {
+            if (!same_base(sp.base, sb)) {
+                if (sb[0] != -(1 << 30))
+                    flush();
+                for (int a = 0; a < 3; ++a)
+                    sb[a] = sp.base[a];
+                sc = hn;
+                s_in = in;
+                for (int n = 0; n < SN; ++n) {
+                    sm[n] = (R)0;
+                    sp_[n][0] = sp_[n][1] = sp_[n][2] = (R)0;
+                }
+            }
+        }
+        if constexpr (SC) {
+            for (int k = 0; k < NS; ++k)
+                for (int j = 0; j < NS; ++j)
+                    for (int i = 0; i < NS; ++i) {
+                        const R N = sp.w[0][i] * sp.w[1][j] * sp.w[2][k];
+                        const int n = i + 2 * j + 4 * k;
+                        sm[n] += N * mp;
+                        for (int a = 0; a < 3; ++a)
+                            sp_[n][a] += N * mv[a];
+                    }
+        } else {
+            scatter(sp, nc, in, mp, mv);
+        }
+    }
+    if constexpr (OVERLAY) {
+        // every gather from the tile is done: the same LDS now accumulates
+        __syncthreads();
+        for (int q = threadIdx.x; q < ACAP; q += blockDim.x)
+            acc[0][q] = acc[1][q] = acc[2][q] = acc[3][q] = 0.0;
+        __syncthreads();
+        // particles rr and rr + 1 of a thread are successive particles of
+        // one cell in level-major order, and most stay in it: such a pair
+        // shares one set of anchored adds (half the LDS atomics)
+#pragma unroll
+        for (int rr = 0; rr < KP; rr += 2) {
+            if (rr + 1 < KP && mvd[rr].ok && mvd[rr + 1].ok && mvd[rr].in && mvd[rr + 1].in &&
+                same_base(mvd[rr].c, mvd[rr + 1].c)) {
+                Support<R, SH> sa, sb;
+                make_support<R, SH>(S, mvd[rr].x, mvd[rr].c, sa);
+                make_support<R, SH>(S, mvd[rr + 1].x, mvd[rr + 1].c, sb);
+                scatter_pair(sa, sb, mvd[rr].c, mvd[rr].m, mvd[rr].mv, mvd[rr + 1].m, mvd[rr + 1].mv);
+                continue;
+            }
+#pragma unroll
+            for (int r2 = rr; r2 < rr + 2 && r2 < KP; ++r2)
+                if (mvd[r2].ok) {
+                    Support<R, SH> sq;
+                    make_support<R, SH>(S, mvd[r2].x, mvd[r2].c, sq);
+                    scatter(sq, mvd[r2].c, mvd[r2].in, mvd[r2].m, mvd[r2].mv);
+                }
+        }
+    }
+    if constexpr (SC)
+        if (sb[0] != -(1 << 30))
+            flush();
+    int blo[3], bhi[3];
+    item_box<T>(mn, mx, red, blo, bhi);
+    // flush the home-tile entries the moved particles can have touched
+    // (their cells' node box), zeroing them for the next item
+    const Tile nbx = tile_of_cells<SH>(blo, bhi);
+    Tile fb;   // nbx within the home tile, in home-tile coordinates
+    for (int a = 0; a < 3; ++a) {
+        fb.lo[a] = max(nbx.lo[a], ht.lo[a]) - ht.lo[a];
+        fb.dim[a] = max(min(nbx.lo[a] + nbx.dim[a], ht.lo[a] + HD) - ht.lo[a] - fb.lo[a], 0);
+    }
+    const int fv = fb.dim[0] * fb.dim[1] * fb.dim[2];
+    for (int q = threadIdx.x; q < fv; q += blockDim.x) {
+        int a, b, c;
+        tile_node_small(fb, q, a, b, c);
+        const int li = a + APX * b + APXY * c;
+        const double m = acc[0][li];
+        const int i = ht.lo[0] + a, j = ht.lo[1] + b, k = ht.lo[2] + c;
+        if (m != 0.0 && node_in_mesh(S, i, j, k)) {
+            const uint32_t I = node_id(S, i, j, k);
+            addg(nn.m, I, m);
+            for (int e = 0; e < 3; ++e)
+                addg(nn.p[e], I, (R)acc[1 + e][li]);
+        }
+        if constexpr (!OVERLAY)
+            acc[0][li] = acc[1][li] = acc[2][li] = acc[3][li] = 0.0;
+    }
+    __syncthreads();
+    return Moves{err, lost, drift, nbx};
 }
 
 // USF: particle velocity (FLIP/PIC) and position from the nodal acceleration
@@ -2984,37 +3453,14 @@ __device__ inline void load_update_tile_packed(const SceneDev &S, const NodeBuf<
 template <typename R, int SH, int T>
 __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 {
-    constexpr int NS = ShapeTraits<SH>::NS;
-    constexpr int CAP = ShapeTraits<SH>::cap;
-    constexpr int KP = kChunk / T;
-    using C = Cache<SH, kG2PCacheGather, kG2PCacheScatter>;
-    constexpr bool GC = C::gather, SC = C::scatter;
-    constexpr int GN = C::gnodes, SN = C::snodes;
-    // GIMP: the gather tile and the scatter accumulators share LDS (all
-    // particles are updated before the scatter starts), which admits one
-    // more workgroup per CU
-    constexpr bool OVERLAY = SH == 1;
-    // home-tile accumulators: edge HD, at row and plane pitches APX, APXY
-    // (GIMP: the anchored layout, see kAnchPX)
-    constexpr int HD = kBrick + 2 + ShapeTraits<SH>::lo + ShapeTraits<SH>::hi;   // home tile edge
-    constexpr int APX = SH == 1 ? kAnchPX : HD, APXY = SH == 1 ? kAnchPXY : HD * HD;
-    constexpr int ACAP = APXY * HD;
-    static_assert(SH != 1 || (HD == 9 && ACAP == kAnchCap), "anchored layout holds the GIMP home tile");
-    // the gather tile packs a node's acceleration and updated velocity in
-    // 24 bytes (FP32), which leaves room for one more workgroup per CU
-    constexpr int TILE_BYTES = CAP * (int)(sizeof(R4<R>) + sizeof(R2<R>)), ACC_BYTES = 4 * ACAP * (int)sizeof(double);
-    static_assert((CAP * sizeof(R4<R>)) % alignof(R2<R>) == 0 && TILE_BYTES % alignof(double) == 0, "tile alignment");
-    __shared__ __attribute__((aligned(16))) char lds[OVERLAY ? (TILE_BYTES > ACC_BYTES ? TILE_BYTES : ACC_BYTES)
-                                                             : TILE_BYTES + ACC_BYTES];
-    R4<R> *la = (R4<R> *)lds;
-    R2<R> *lyz = (R2<R> *)(lds + CAP * sizeof(R4<R>));
-    double (*acc)[ACAP] = (double (*)[ACAP])(lds + (OVERLAY ? 0 : TILE_BYTES));
+    __shared__ G2pLds<R, SH> lds;
     __shared__ int red[6 * (T / 64)];
     // the accumulators start at zero, and each item's flush leaves them so
     // (with OVERLAY the tile overwrites them, so every item zeroes them)
-    if constexpr (!OVERLAY)
-        for (int q = threadIdx.x; q < ACAP; q += blockDim.x)
-            acc[0][q] = acc[1][q] = acc[2][q] = acc[3][q] = 0.0;
+    if constexpr (!G2pLds<R, SH>::OVERLAY)
+        for (int q = threadIdx.x; q < G2pLds<R, SH>::ACAP; q += blockDim.x)
+            for (int a = 0; a < 4; ++a)
+                lds.acc()[a][q] = 0.0;
     const int64_t total = B.ioffs[B.nscenes];
     const ItemRange ir = item_range(total);
     for (int64_t g = ir.first; g < ir.end; g += ir.step) {
@@ -3031,354 +3477,502 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
         const Parts<R> P = parts<R>(S, cur);
         const NodeBuf<R> nb = node_buf<R>(S, buf);
         const NodeBuf<R> nn = node_buf<R>(S, nbuf);
-        int o[3];
-        brick_origin(S, item.brick, o);
-        const Tile ht = home_tile<SH>(o);
-        load_update_tile_packed<R>(S, nb, t, la, lyz);
-        __syncthreads();
-        const R dt = cst<R>(S.dt, S.f_dt);
-        const int pic = S.vel_update == 1;
-        uint32_t err = 0, drift = 0, lost = 0;
-        int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
-        // gather cache (old support) and scatter cache (new support)
-        int gb[3] = {-(1 << 30), 0, 0}, sb[3] = {-(1 << 30), 0, 0};
-        R ca[GN][3], cu[GN][3], sp_[SN][3], sm[SN];
-        Corners sc{};
-        bool s_in = true;
-        // the moved particles awaiting the scatter (OVERLAY)
-        struct Moved {
-            double x[3];
-            R m, mv[3];
-            int c[3];
-            bool ok, in;
-        };
-        Moved mvd[OVERLAY ? KP : 1];
-        if constexpr (OVERLAY)
-            for (int rr = 0; rr < KP; ++rr)
-                mvd[rr].ok = false;
-        // next step's mass and momentum of one particle with support sp:
-        // into the home tile's accumulators, or (drifted) global memory
-        auto scatter = [&](const Support<R, SH> &sq, const int cq[3], bool inh, R m, const R mvq[3]) {
-            const Corners hq = corners(S, ht, sq.base);
-            if (SH == 1 && inh) {
-                // anchored 4 x 4 x 4 slots (see kAnchPX); home-tile coordinates
-                // of node c - 1 are c - o + 1 in [0, 5] for a cell in the home region
-                R w4[3][4], dw4[3][4];
-                for (int a = 0; a < 3; ++a)
-                    anchor4<R>(sq.w[a], sq.dw[a], sq.base[a] == cq[a] ? 1 : 0, w4[a], dw4[a]);
-                const int a0 = (cq[0] - 1 - ht.lo[0]) + APX * (cq[1] - 1 - ht.lo[1]) + APXY * (cq[2] - 1 - ht.lo[2]);
-                for (int k = 0; k < 4; ++k)
-                    for (int j = 0; j < 4; ++j) {
-                        const R wyz = w4[1][j] * w4[2][k];
-                        for (int i = 0; i < 4; ++i) {
-                            const R N = w4[0][i] * wyz;
-                            const int li = a0 + i + APX * j + APXY * k;
-                            atomicAdd(&acc[0][li], (double)(N * m));
-                            atomicAdd(&acc[1][li], (double)(N * mvq[0]));
-                            atomicAdd(&acc[2][li], (double)(N * mvq[1]));
-                            atomicAdd(&acc[3][li], (double)(N * mvq[2]));
-                        }
-                        __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
-                    }
-            } else if (inh) {
-                for (int k = 0; k < NS; ++k)
-                    for (int j = 0; j < NS; ++j)
-                        for (int i = 0; i < NS; ++i) {
-                            const R N = sq.w[0][i] * sq.w[1][j] * sq.w[2][k];
-                            const int li = hq.t0 + i + j * hq.ty + k * hq.tz;
-                            atomicAdd(&acc[0][li], (double)(N * m));
-                            atomicAdd(&acc[1][li], (double)(N * mvq[0]));
-                            atomicAdd(&acc[2][li], (double)(N * mvq[1]));
-                            atomicAdd(&acc[3][li], (double)(N * mvq[2]));
-                        }
-            } else {
-                for (int k = 0; k < NS; ++k)
-                    for (int j = 0; j < NS; ++j)
-                        for (int i = 0; i < NS; ++i) {
-                            const R N = sq.w[0][i] * sq.w[1][j] * sq.w[2][k];
-                            const uint32_t I = hq.n0 + (uint32_t)(i + j * hq.ny + k * hq.nz);
-                            addg(nn.m, I, (double)(N * m));
-                            for (int a = 0; a < 3; ++a)
-                                addg(nn.p[a], I, N * mvq[a]);
-                        }
-            }
-        };
-        // two particles in one home cell (GIMP): one set of anchored adds
-        // carries the sum of their contributions
-        auto scatter_pair = [&](const Support<R, SH> &sa, const Support<R, SH> &sb, const int cq[3], R ma,
-                                const R mva[3], R mb, const R mvb[3]) {
-            R wa[3][4], wb[3][4], unused[4];
-            for (int a = 0; a < 3; ++a) {
-                anchor4<R>(sa.w[a], sa.dw[a], sa.base[a] == cq[a] ? 1 : 0, wa[a], unused);
-                anchor4<R>(sb.w[a], sb.dw[a], sb.base[a] == cq[a] ? 1 : 0, wb[a], unused);
-            }
-            const int a0 = (cq[0] - 1 - ht.lo[0]) + APX * (cq[1] - 1 - ht.lo[1]) + APXY * (cq[2] - 1 - ht.lo[2]);
-            for (int k = 0; k < 4; ++k)
-                for (int j = 0; j < 4; ++j) {
-                    const R ya = wa[1][j] * wa[2][k], yb = wb[1][j] * wb[2][k];
-                    for (int i = 0; i < 4; ++i) {
-                        const R Na = wa[0][i] * ya, Nb = wb[0][i] * yb;
-                        const int li = a0 + i + APX * j + APXY * k;
-                        atomicAdd(&acc[0][li], (double)(Na * ma + Nb * mb));
-                        atomicAdd(&acc[1][li], (double)(Na * mva[0] + Nb * mvb[0]));
-                        atomicAdd(&acc[2][li], (double)(Na * mva[1] + Nb * mvb[1]));
-                        atomicAdd(&acc[3][li], (double)(Na * mva[2] + Nb * mvb[2]));
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
-                }
-        };
-        auto flush = [&]() {
-            for (int n = 0; n < SN; ++n) {
-                const int di = n & 1, dj = (n >> 1) & 1, dk = n >> 2;
-                if (s_in) {
-                    const int li = sc.t0 + di + dj * sc.ty + dk * sc.tz;
-                    atomicAdd(&acc[0][li], (double)sm[n]);
-                    for (int a = 0; a < 3; ++a)
-                        atomicAdd(&acc[1 + a][li], (double)sp_[n][a]);
-                } else {
-                    const uint32_t I = sc.n0 + (uint32_t)(di + dj * sc.ny + dk * sc.nz);
-                    addg(nn.m, I, (double)sm[n]);
-                    for (int a = 0; a < 3; ++a)
-                        addg(nn.p[a], I, sp_[n][a]);
-                }
-            }
-        };
-#pragma unroll
-        for (int rr = 0; rr < KP; ++rr) {
-            const uint32_t q = threadIdx.x + rr * T;
-            if (q >= item.count)
-                break;
-            const uint32_t p = item.start + q;
-            double xp[3] = {ldg(P.x[0], p), ldg(P.x[1], p), ldg(P.x[2], p)};
-            const R pv[3] = {ldg(P.v[0], p), ldg(P.v[1], p), ldg(P.v[2], p)};
-            const R mp = ldg(P.mass, p);
-            const uint32_t pc = ldg(P.cell, p);
-            __builtin_amdgcn_sched_barrier(0);   // the particle's loads in one round trip
-            int c[3];
-            unpack_cell(pc, c);
-            Support<R, SH> sp;
-            IsoAt iso;
-            if constexpr (SH == 2)
-                iso_at<R>(S, xp, c, sp, iso);
-            else
-                make_support<R, SH>(S, xp, c, sp);
-            pin_loaded(pv);
-            const Corners cn = corners(S, t, sp.base);
-            if constexpr (GC) {
-                if (!same_base(sp.base, gb)) {
-                    for (int a = 0; a < 3; ++a)
-                        gb[a] = sp.base[a];
-                    for (int n = 0; n < GN; ++n) {
-                        const int li = cn.t0 + (n & 1) + ((n >> 1) & 1) * cn.ty + (n >> 2) * cn.tz;
-                        const R4<R> a4 = la[li];
-                        const R2<R> u2 = lyz[li];
-                        ca[n][0] = a4.x;
-                        ca[n][1] = a4.y;
-                        ca[n][2] = a4.z;
-                        cu[n][0] = a4.w;
-                        cu[n][1] = u2.s;
-                        cu[n][2] = u2.t;
-                    }
-                }
-            }
-            R dv[3] = {0, 0, 0}, vp[3] = {0, 0, 0};
-            for (int k = 0; k < NS; ++k)
-                for (int j = 0; j < NS; ++j)
-                    for (int i = 0; i < NS; ++i) {
-                        const R N = sp.w[0][i] * sp.w[1][j] * sp.w[2][k];
-                        R a[3], u[3];
-                        if constexpr (GC) {
-                            const int n = i + 2 * j + 4 * k;
-                            for (int e = 0; e < 3; ++e) {
-                                a[e] = ca[n][e];
-                                u[e] = cu[n][e];
-                            }
-                        } else {
-                            const int li = cn.t0 + i + j * cn.ty + k * cn.tz;
-                            const R4<R> a4 = la[li];
-                            const R2<R> u2 = lyz[li];
-                            a[0] = a4.x;
-                            a[1] = a4.y;
-                            a[2] = a4.z;
-                            u[0] = a4.w;
-                            u[1] = u2.s;
-                            u[2] = u2.t;
-                        }
-                        for (int e = 0; e < 3; ++e) {
-                            dv[e] += N * a[e];
-                            vp[e] += N * u[e];
-                        }
-                        if constexpr (SH == 1)
-                            if (i == NS - 1)
-                                __builtin_amdgcn_sched_barrier(0);   // one support layer of LDS reads in flight
-                    }
-            R nv[3];
-            double dx[3];
-            for (int a = 0; a < 3; ++a) {
-                nv[a] = pic ? vp[a] : pv[a] + dt * dv[a];
-                stg(P.v[a], p, nv[a]);
-                dx[a] = S.dt * (double)vp[a];
-                xp[a] += dx[a];
-                stg(P.x[a], p, xp[a]);
-                if (!isfinite(nv[a]))
-                    err |= ERR_NONFINITE;
-            }
-            int nc[3];
-            double fr[3];
-            uint32_t e;
-            if constexpr (SH == 2) {   // walk from the old cell; fr: local coordinates in the new one
-                for (int a = 0; a < 3; ++a)
-                    nc[a] = c[a];
-                e = iso_moved(S, xp, dx, nc, iso);
-                for (int a = 0; a < 3; ++a)
-                    fr[a] = iso.r[a];
-            } else {
-                e = locate<SH == 0>(S, xp, nc, fr);
-            }
-            if (e) {
-                err |= e;   // keep the old cell; the scene stops after this step
-                lost += (e & ERR_OUT_OF_MESH) ? 1u : 0u;
-                continue;
-            }
-            stg(P.cell, p, pack_cell(nc));
-            for (int a = 0; a < 3; ++a) {
-                mn[a] = min(mn[a], nc[a]);
-                mx[a] = max(mx[a], nc[a]);
-            }
-            const bool in = in_home(nc, o);
-            drift |= in ? 0u : 1u;
-            if constexpr (OVERLAY) {
-                Moved &mq = mvd[rr];
-                for (int a = 0; a < 3; ++a) {
-                    mq.x[a] = xp[a];
-                    mq.c[a] = nc[a];
-                    mq.mv[a] = mp * nv[a];
-                }
-                mq.m = mp;
-                mq.in = in;
-                mq.ok = true;
-                continue;
-            }
-            // the next step's P2G from the updated particle (trilinear: the
-            // local coordinate is the cell search's fractional part, or the
-            // isoparametric walk's local coordinates)
-            if constexpr (SH != 1) {
-                const R ih = cst<R>(S.inv_h, S.f_inv_h);
-                for (int a = 0; a < 3; ++a) {
-                    const R r = (R)fr[a];
-                    sp.base[a] = nc[a];
-                    sp.w[a][0] = (R)1 - r;
-                    sp.w[a][1] = r;
-                    sp.dw[a][0] = -ih;
-                    sp.dw[a][1] = ih;
-                }
-            } else {
-                make_support<R, SH>(S, xp, nc, sp);
-            }
-            const Corners hn = corners(S, ht, sp.base);
-            const R mv[3] = {mp * nv[0], mp * nv[1], mp * nv[2]};
-            if constexpr (SC) {
-                if (!same_base(sp.base, sb)) {
-                    if (sb[0] != -(1 << 30))
-                        flush();
-                    for (int a = 0; a < 3; ++a)
-                        sb[a] = sp.base[a];
-                    sc = hn;
-                    s_in = in;
-                    for (int n = 0; n < SN; ++n) {
-                        sm[n] = (R)0;
-                        sp_[n][0] = sp_[n][1] = sp_[n][2] = (R)0;
-                    }
-                }
-            }
-            if constexpr (SC) {
-                for (int k = 0; k < NS; ++k)
-                    for (int j = 0; j < NS; ++j)
-                        for (int i = 0; i < NS; ++i) {
-                            const R N = sp.w[0][i] * sp.w[1][j] * sp.w[2][k];
-                            const int n = i + 2 * j + 4 * k;
-                            sm[n] += N * mp;
-                            for (int a = 0; a < 3; ++a)
-                                sp_[n][a] += N * mv[a];
-                        }
-            } else {
-                scatter(sp, nc, in, mp, mv);
-            }
-        }
-        if constexpr (OVERLAY) {
-            // every gather from the tile is done: the same LDS now accumulates
-            __syncthreads();
-            for (int q = threadIdx.x; q < ACAP; q += blockDim.x)
-                acc[0][q] = acc[1][q] = acc[2][q] = acc[3][q] = 0.0;
-            __syncthreads();
-            // particles rr and rr + 1 of a thread are successive particles of
-            // one cell in level-major order, and most stay in it: such a pair
-            // shares one set of anchored adds (half the LDS atomics)
-#pragma unroll
-            for (int rr = 0; rr < KP; rr += 2) {
-                if (rr + 1 < KP && mvd[rr].ok && mvd[rr + 1].ok && mvd[rr].in && mvd[rr + 1].in &&
-                    same_base(mvd[rr].c, mvd[rr + 1].c)) {
-                    Support<R, SH> sa, sb;
-                    make_support<R, SH>(S, mvd[rr].x, mvd[rr].c, sa);
-                    make_support<R, SH>(S, mvd[rr + 1].x, mvd[rr + 1].c, sb);
-                    scatter_pair(sa, sb, mvd[rr].c, mvd[rr].m, mvd[rr].mv, mvd[rr + 1].m, mvd[rr + 1].mv);
-                    continue;
-                }
-#pragma unroll
-                for (int r2 = rr; r2 < rr + 2 && r2 < KP; ++r2)
-                    if (mvd[r2].ok) {
-                        Support<R, SH> sq;
-                        make_support<R, SH>(S, mvd[r2].x, mvd[r2].c, sq);
-                        scatter(sq, mvd[r2].c, mvd[r2].in, mvd[r2].m, mvd[r2].mv);
-                    }
-            }
-        }
-        if constexpr (SC)
-            if (sb[0] != -(1 << 30))
-                flush();
-        if (err)
-            atomicOr(&S.ctl[CTL_ERR], err);
-        if (lost)
-            atomicAdd(&S.ctl[CTL_LOST], lost);
-        if (drift || (S.sort_always && threadIdx.x == 0)) {
+        const Moves mv = g2p_item<R, SH, T, PLAIN>(S, item, P, nb, nn, t, lds, red, -1);
+        if (mv.err)
+            atomicOr(&S.ctl[CTL_ERR], mv.err);
+        if (mv.lost)
+            atomicAdd(&S.ctl[CTL_LOST], mv.lost);
+        if (mv.drift || (S.sort_always && threadIdx.x == 0)) {
             S.ctl[CTL_NEED_SORT] = 1u;
             B.flags[BF_ANY_SORT] = 1u;
         }
-        int blo[3], bhi[3];
-        item_box<T>(mn, mx, red, blo, bhi);
         if (threadIdx.x == 0) {
-            pick(S.tiles, nbuf)[r.it] = tile_of_cells<SH>(blo, bhi);
+            pick(S.tiles, nbuf)[r.it] = mv.box;
             if (r.it == 0) {
                 S.ctl[CTL_ACC0 + nbuf] = S.ctl[CTL_N_ITEMS];
                 S.ctl[CTL_READY] = 1u;
             }
         }
-        // flush the home-tile entries the moved particles can have touched
-        // (their cells' node box), zeroing them for the next item
-        const Tile nbx = tile_of_cells<SH>(blo, bhi);
-        Tile fb;   // nbx within the home tile, in home-tile coordinates
-        for (int a = 0; a < 3; ++a) {
-            fb.lo[a] = max(nbx.lo[a], ht.lo[a]) - ht.lo[a];
-            fb.dim[a] = max(min(nbx.lo[a] + nbx.dim[a], ht.lo[a] + HD) - ht.lo[a] - fb.lo[a], 0);
+    }
+}
+
+// ------------------------------------------------ many steps, one launch --
+// k_steps runs the remaining steps of a small USF batch in one launch: one
+// workgroup per compute unit, each keeping its items (and their particles)
+// from step to step.  The two stages of a step are separated by a grid
+// barrier in place of the kernel boundaries, and the step control and the
+// items' start are paid once.  Between workgroups only the node buffers are
+// shared: they are written with agent-scope atomics (adds, and the zeroing)
+// and read with agent-scope atomic loads, so the barrier needs no cache
+// write-back or invalidation: every wavefront waits until its own accesses
+// have completed, then its workgroup arrives.  Measured on a probe of this
+// pattern (arrival, wait and a 1 KB exchange): 2.5 us from 8 to 256
+// workgroups, 18 us with fences in place of the atomics.
+//
+// A step that raises an error or lets a particle drift past its home region
+// is an event, which the barrier reports to every workgroup.  They then meet
+// once more with fences, the first workgroup brings the control blocks up to
+// date, reorders the scenes that need it and publishes the next work list.
+//
+// A barrier completes only if every workgroup it counts is running, and other
+// kernels may hold part of the device for any time (other launches of this
+// one, too).  So the team is made of the workgroups that have started: each
+// takes a number as it starts, and the first one, which publishes the work
+// lists, publishes with each how many take part (waiting kStartTicks for the
+// rest before the first list).  Later ones wait for a list that counts them;
+// the first workgroup makes an event of their start.  Nobody waits for a
+// workgroup that may not be running.
+//
+// A step is bound by the chain of latencies of one item's two stages (about
+// 5 us each) and two barriers.  512 threads, one particle each, keep that
+// chain shortest (no loop over particles).  Measured per step against the
+// separate kernels: 1000 particles 18.9 -> 14.6 us (GIMP 29.1 -> 24.4, FP64
+// 18.9 -> 16.7, isoparametric 25.1 -> 20.0), 51200 particles 22.0 -> 16.8 us.
+
+constexpr uint64_t kStartTicks = 10000ull;       // 100 us of the 100 MHz wall clock
+constexpr uint64_t kStepTicks = 1000000000ull;   // 10 s: bound of a wait for running workgroups, which end far earlier
+
+struct Team {
+    uint32_t *flags;
+    uint32_t id;                      // this workgroup's number
+    uint32_t n, ng, group, members;   // workgroups of the current list, their groups, this one's group and its size
+    uint32_t gen, gen0;               // barriers passed; those before the current list
+    uint32_t events;                  // events reported so far
+    uint32_t list;                    // lists published so far
+    uint32_t left;                    // steps left to this launch
+    bool ok;                          // no wait gave up
+};
+
+__device__ inline uint64_t live64(const uint32_t *p)
+{
+    return __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ inline void set_live64(uint32_t *p, uint64_t v)
+{
+    __hip_atomic_store((unsigned long long *)p, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Wait for every workgroup of the team; true if one of them reported an event
+// (event: of any of the calling workgroup's threads).  Each wavefront's memory
+// accesses have completed before its workgroup arrives.  With FENCE, plain
+// stores included, what a workgroup wrote before is visible to those that
+// take up a list published after.
+template <bool FENCE = false>
+__device__ inline bool barrier_wait(Team &b, bool event, uint32_t (*sh)[5])
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    const bool any = __syncthreads_or(event ? 1 : 0) != 0;
+    ++b.gen;
+    if (threadIdx.x == 0) {
+        if constexpr (FENCE)
+            __threadfence();
+        unsigned long long *root = (unsigned long long *)&b.flags[BF_STEP_ROOT];
+        if (any) {
+            // counted before this workgroup arrives
+            atomicAdd(root, 1ull << 32);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
-        const int fv = fb.dim[0] * fb.dim[1] * fb.dim[2];
-        for (int q = threadIdx.x; q < fv; q += blockDim.x) {
-            int a, b, c;
-            tile_node_small(fb, q, a, b, c);
-            const int li = a + APX * b + APXY * c;
-            const double m = acc[0][li];
-            const int i = ht.lo[0] + a, j = ht.lo[1] + b, k = ht.lo[2] + c;
-            if (m != 0.0 && node_in_mesh(S, i, j, k)) {
-                const uint32_t I = node_id(S, i, j, k);
-                addg(nn.m, I, m);
-                for (int e = 0; e < 3; ++e)
-                    addg(nn.p[e], I, (R)acc[1 + e][li]);
+        const uint32_t turn = b.gen - b.gen0;
+        if (atomicAdd(&b.flags[BF_STEP_GROUP + 32 * b.group], 1u) + 1u == turn * b.members) {
+            const unsigned long long r = atomicAdd(root, 1ull) + 1ull;
+            if ((uint32_t)r == turn * b.ng)
+                for (uint32_t q = 0; q < b.ng; ++q)
+                    set_live64(&b.flags[BF_STEP_RELEASE + 32 * q], (r & 0xffffffff00000000ull) | b.gen);
+        }
+        const uint64_t t0 = wall_clock64();
+        uint64_t w;
+        uint32_t good = 1u;
+        while ((uint32_t)(w = live64(&b.flags[BF_STEP_RELEASE + 32 * b.group])) < b.gen) {
+            if (wall_clock64() - t0 > kStepTicks) {
+                good = 0u;
+                break;
             }
-            if constexpr (!OVERLAY)
-                acc[0][li] = acc[1][li] = acc[2][li] = acc[3][li] = 0.0;
+            __builtin_amdgcn_s_sleep(1);
         }
+        (*sh)[0] = (uint32_t)(w >> 32);
+        (*sh)[1] = good;
+    }
+    __syncthreads();
+    const uint32_t events = (*sh)[0];
+    b.ok = b.ok && (*sh)[1] != 0u;
+    const bool ev = events != b.events;
+    b.events = events;
+    __syncthreads();   // sh is rewritten by the next wait
+    return ev;
+}
+
+// This workgroup's number; the first one waits a while for the others.
+__device__ inline Team join_team(uint32_t *flags, uint32_t (*sh)[5])
+{
+    if (threadIdx.x == 0) {
+        const uint32_t id = atomicAdd(&flags[BF_STEP_START], 1u);
+        if (id == 0) {
+            const uint64_t t0 = wall_clock64();
+            while (live(&flags[BF_STEP_START]) < gridDim.x && wall_clock64() - t0 <= kStartTicks)
+                __builtin_amdgcn_s_sleep(1);
+        }
+        (*sh)[0] = id;
+    }
+    __syncthreads();
+    Team b;
+    b.flags = flags;
+    b.id = uni((*sh)[0]);
+    b.n = b.ng = b.group = b.members = 0;
+    b.gen = b.gen0 = b.events = b.list = b.left = 0;
+    b.ok = true;
+    __syncthreads();
+    return b;
+}
+
+// Publish the next work list (its data is in memory, made by the calling
+// first workgroup): the workgroups started so far take part; with end, none,
+// and all of them finish.  Every member of the last list is past its last
+// barrier or waits for its release word, which keeps its value.
+__device__ inline void publish_list(const Team &b, bool end)
+{
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t n = end ? 0u : live(&b.flags[BF_STEP_START]);
+        set_live64(&b.flags[BF_STEP_ROOT], (uint64_t)b.events << 32);
+        for (int q = 0; q < kXcds; ++q)
+            set_live(&b.flags[BF_STEP_GROUP + 32 * q], 0u);
+        set_live64(&b.flags[BF_STEP_INFO], (uint64_t)b.events << 32 | b.gen);
+        set_live(&b.flags[BF_STEP_LEFT], b.left);
+        __threadfence();
+        set_live64(&b.flags[BF_STEP_LIST], (uint64_t)n << 32 | (b.list + 1u));
+    }
+    __syncthreads();
+}
+
+// Wait for the next list that counts this workgroup; false at the end.
+__device__ inline bool take_list(Team &b, uint32_t (*sh)[5])
+{
+    if (threadIdx.x == 0) {
+        uint64_t w;
+        uint32_t n = 0u;
+        const uint64_t t0 = wall_clock64();
+        for (;;) {
+            w = live64(&b.flags[BF_STEP_LIST]);
+            n = (uint32_t)(w >> 32);
+            if ((uint32_t)w > b.list && (n == 0u || n > b.id))
+                break;
+            if (wall_clock64() - t0 > kStepTicks) {
+                n = 0u;
+                w = 0;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+        }
+        __threadfence();
+        const uint64_t info = live64(&b.flags[BF_STEP_INFO]);
+        (*sh)[0] = n;
+        (*sh)[1] = (uint32_t)w;
+        (*sh)[2] = (uint32_t)info;
+        (*sh)[3] = (uint32_t)(info >> 32);
+        (*sh)[4] = live(&b.flags[BF_STEP_LEFT]);
+    }
+    __syncthreads();
+    b.left = uni((*sh)[4]);
+    b.n = uni((*sh)[0]);
+    b.list = uni((*sh)[1]);
+    b.gen = b.gen0 = uni((*sh)[2]);
+    b.events = uni((*sh)[3]);
+    b.ok = b.ok && b.list != 0u;
+    b.ng = min(b.n, (uint32_t)kXcds);
+    if (b.ng) {
+        b.group = b.id % b.ng;
+        b.members = b.n / b.ng + (b.group < b.n % b.ng ? 1u : 0u);
+    }
+    __syncthreads();
+    return b.n != 0u;
+}
+
+// The first workgroup, while the others wait: the control blocks after `done`
+// more steps of the active scenes, the reorder of those that need one (the
+// particles are then visible to this workgroup), which scenes go on, and
+// their item offsets.  Returns the number of items.
+template <typename R>
+__device__ uint32_t steps_control(const BatchDev &B, uint32_t done, char *lds)
+{
+    uint32_t *scan = (uint32_t *)lds;
+    __shared__ int any;
+    if (threadIdx.x == 0)
+        any = 0;
+    __syncthreads();
+    for (int s = threadIdx.x; s < B.nscenes; s += blockDim.x) {
+        uint32_t *c = B.ctls[s];
+        auto get = [&](int w) { return __hip_atomic_load(&c[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        if (!get(CTL_ACTIVE))
+            continue;
+        const uint32_t remain = get(CTL_REMAIN), adv = min(remain, done);
+        set_live(&c[CTL_REMAIN], remain - adv);
+        set_live(&c[CTL_STEPS], get(CTL_STEPS) + adv);
+        set_live(&c[CTL_NBUF], get(CTL_NBUF) ^ (adv & 1u));
+        if (adv) {
+            set_live(&c[CTL_ACC0], get(CTL_N_ITEMS));
+            set_live(&c[CTL_ACC1], get(CTL_N_ITEMS));
+        }
+        const bool go = get(CTL_ERR) == 0u && remain > adv;
+        set_live(&c[CTL_ACTIVE], go ? 1u : 0u);
+        if (go && get(CTL_NEED_SORT))
+            any = 1;
+    }
+    __threadfence();
+    __syncthreads();
+    if (any) {
+        // the reorder's phases, each as one chunk of this workgroup
+        const uint32_t nb = (uint32_t)B.total_bricks, nw = blockDim.x >> 6;
+        auto phase = [&]() {
+            __threadfence();
+            __syncthreads();
+            __threadfence();
+        };
+        sort_count(B, 0, 1);
+        phase();
+        sort_bricks(B, 0, 0, nb);
+        phase();
+        scan_finish(B, 0, 0, nb, (Seg *)lds);
+        phase();
+        sort_perm(B, 0, 1);
+        phase();
+        sort_move<R>(B, uni(threadIdx.x >> 6), nw, live(&B.flags[BF_NBRICKS]));
+        phase();
+        for (int s = threadIdx.x; s < B.nscenes; s += blockDim.x) {
+            uint32_t *c = B.ctls[s];
+            auto get = [&](int w) { return __hip_atomic_load(&c[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            if (get(CTL_ACTIVE) && get(CTL_NEED_SORT)) {
+                set_live(&c[CTL_CUR], get(CTL_CUR) ^ 1u);
+                set_live(&c[CTL_NEED_SORT], 0u);
+                set_live(&c[CTL_N_SORTS], get(CTL_N_SORTS) + 1u);
+            }
+        }
+        __threadfence();
         __syncthreads();
     }
+    // item offsets of the scenes that go on
+    uint32_t carry = 0;
+    if (threadIdx.x == 0)
+        set_live(&B.ioffs[0], 0u);
+    for (int base = 0; base < B.nscenes; base += blockDim.x) {
+        const int s = base + threadIdx.x;
+        uint32_t n = 0;
+        if (s < B.nscenes) {
+            const uint32_t *c = B.ctls[s];
+            n = __hip_atomic_load(&c[CTL_ACTIVE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                    ? __hip_atomic_load(&c[CTL_N_ITEMS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                    : 0u;
+        }
+        scan[threadIdx.x] = n;
+        __syncthreads();
+        for (uint32_t o = 1; o < blockDim.x; o <<= 1) {
+            const uint32_t a = threadIdx.x >= o ? scan[threadIdx.x - o] : 0u;
+            __syncthreads();
+            scan[threadIdx.x] += a;
+            __syncthreads();
+        }
+        if (s < B.nscenes)
+            set_live(&B.ioffs[s + 1], carry + scan[threadIdx.x]);
+        carry += scan[blockDim.x - 1];
+        __syncthreads();
+    }
+    return carry;
+}
+
+// An item of the current work list with what its stages need of its scene.
+// The workgroup that runs it keeps it in LDS from step to step.
+struct Slot {
+    const SceneDev *S;
+    uint32_t it;
+    uint32_t remain;         // steps the scene had left when the list was made
+    uint32_t cur, nbuf;      // particle buffer; node buffer of the step before the list was made
+    uint32_t steps;          // steps completed then
+    uint32_t n_items, acc;   // the scene's items; boxes recorded for node buffer nbuf
+    Item item;
+    Tile tile[2];            // boxes the node buffers' data were accumulated over (tile[nbuf]: the acc boxes' own)
+};
+
+constexpr int kSlots = 8;   // items a workgroup keeps; with more it loads them again for every stage
+
+// Slots of items id + (base + m) n, m < kSlots, below total, with the boxes
+// recorded last.
+__device__ inline void load_slots(const BatchDev &B, const Team &b, uint32_t base, uint32_t total, Slot *slots)
+{
+    const uint32_t m = threadIdx.x, g = b.id + (base + m) * b.n;
+    if (m < (uint32_t)kSlots && g < total) {
+        auto get = [](const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        int lo = 0, hi = B.nscenes - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (get(&B.ioffs[mid]) <= g)
+                lo = mid;
+            else
+                hi = mid - 1;
+        }
+        const SceneDev *S = B.scenes[lo];
+        const uint32_t *c = B.ctls[lo];
+        Slot s;
+        s.S = S;
+        s.it = g - get(&B.ioffs[lo]);
+        s.remain = get(&c[CTL_REMAIN]);
+        s.cur = get(&c[CTL_CUR]);
+        s.nbuf = get(&c[CTL_NBUF]);
+        s.steps = get(&c[CTL_STEPS]);
+        s.n_items = get(&c[CTL_N_ITEMS]);
+        s.acc = get(&c[CTL_ACC0 + s.nbuf]);
+        s.item = S->items[s.it];
+        for (int b = 0; b < 2; ++b)
+            s.tile[b] = S->tiles[b][s.it];
+        slots[m] = s;
+    }
+    __syncthreads();
+}
+
+// A slot in scalar registers.
+__device__ inline Slot uni_slot(const Slot &s)
+{
+    static_assert(sizeof(Slot) % 4 == 0, "word-sized struct");
+    Slot out;
+    const uint32_t *src = (const uint32_t *)&s;
+    uint32_t *dst = (uint32_t *)&out;
+    for (int w = 0; w < (int)(sizeof(Slot) / 4); ++w)
+        dst[w] = uni(src[w]);
+    return out;
+}
+
+// Up to `left` steps of every scene of the batch.  On entry one step of the
+// call has run: node buffer CTL_NBUF holds its data and the other one the
+// next step's mass and momentum.
+template <typename R, int SH, int T>
+__global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left)
+{
+    using L1 = StressLds<R, SH>;
+    using L2 = G2pLds<R, SH>;
+    constexpr int KP = kChunk / T;
+    static_assert(KP == 1, "one particle per thread");
+    // the two stages' arrays, and the control's, share LDS
+    constexpr int BYTES = (int)sizeof(L1) > L2::BYTES ? (int)sizeof(L1) : L2::BYTES;
+    static_assert(BYTES >= T * (int)sizeof(Seg), "the control's scans fit");
+    __shared__ __attribute__((aligned(16))) char raw[BYTES];
+    __shared__ int red[6 * (T / 64)];
+    __shared__ uint32_t sh[5];
+    __shared__ Slot slots[kSlots];
+    L1 &l1 = *(L1 *)raw;
+    L2 &l2 = *(L2 *)raw;
+    Team bar = join_team(B.flags, &sh);
+    bar.left = left;
+    uint32_t k = 0;   // steps since the work list was made
+    while (bar.ok) {
+        if (bar.id == 0) {
+            const uint32_t items = steps_control<R>(B, k, raw);
+            publish_list(bar, items == 0u || bar.left == 0u);
+        }
+        if (!take_list(bar, &sh))
+            break;
+        const uint32_t total = live(&B.ioffs[B.nscenes]);
+        const uint32_t mine = total > bar.id ? (total - bar.id - 1u) / bar.n + 1u : 0u;
+        const bool keep = mine <= (uint32_t)kSlots;
+        if (keep)
+            load_slots(B, bar, 0, total, slots);
+        // one stage over the workgroup's items
+        auto each_item = [&](auto stage) {
+            for (uint32_t base = 0; base < mine; base += kSlots) {
+                if (!keep)
+                    load_slots(B, bar, base, total, slots);
+                for (uint32_t m = 0; m < min(mine - base, (uint32_t)kSlots); ++m) {
+                    const Slot s = uni_slot(slots[m]);
+                    if (s.remain > k)
+                        stage(s, slots[m]);
+                }
+            }
+        };
+        bool event = false;
+        for (k = 0; bar.left > 0u && !event && bar.ok; ++k, --bar.left) {
+            // workgroups that have started since take part from the next list
+            bool ev = bar.id == 0u && bar.n < gridDim.x && live(&B.flags[BF_STEP_START]) > bar.n;
+            each_item([&](const Slot &s, Slot &kept) {
+                const SceneDev S = load_scene(s.S);
+                const int buf = (int)((s.nbuf ^ 1u ^ k) & 1u);
+                const Parts<R> P = parts<R>(S, (int)s.cur);
+                uint32_t pcell[KP];
+                pcell[0] = ldg(P.cell, s.item.start + min((uint32_t)threadIdx.x, s.item.count - 1u));
+                const NodeBuf<R> nb = node_buf<R>(S, buf), other = node_buf<R>(S, buf ^ 1);
+                Tile t;
+                if (k > 0) {
+                    t = buf ? s.tile[1] : s.tile[0];
+                    clear_box<R, SHARED>(S, other, buf ? s.tile[0] : s.tile[1]);
+                } else {
+                    // every box of the last step's data, whatever items ran it
+                    for (uint32_t q = s.it; q < s.acc; q += s.n_items) {
+                        Tile old;
+                        const uint32_t *src = (const uint32_t *)&pick(S.tiles, buf ^ 1)[q];
+                        for (int w = 0; w < (int)(sizeof(Tile) / 4); ++w)
+                            ((uint32_t *)&old)[w] = live(&src[w]);
+                        clear_box<R, SHARED>(S, other, old);
+                    }
+                    int mn[3], mx[3], lo[3], hi[3];
+                    unpack_cell(pcell[0], mn);
+                    for (int a = 0; a < 3; ++a)
+                        mx[a] = mn[a];
+                    item_box<T>(mn, mx, red, lo, hi);
+                    t = tile_of_cells<SH>(lo, hi);
+                    if (threadIdx.x == 0) {
+                        kept.tile[buf] = t;
+                        pick(S.tiles, buf)[s.it] = t;
+                    }
+                }
+                uint32_t bad = ERR_TILE;
+                if (t.fits)
+                    bad = stress_item<R, SH, T, SHARED>(S, s.item, P, nb, t, pcell, l1.vxy, l1.vz, l1.f);
+                if (bad) {
+                    atomicOr(&S.ctl[CTL_ERR], bad);
+                    ev = true;
+                }
+                __syncthreads();
+            });
+            barrier_wait(bar, false, &sh);
+            each_item([&](const Slot &s, Slot &kept) {
+                const SceneDev S = load_scene(s.S);
+                const int buf = (int)((s.nbuf ^ 1u ^ k) & 1u);
+                const Tile t = buf ? s.tile[1] : s.tile[0];
+                if (!t.fits)
+                    return;
+                if constexpr (!L2::OVERLAY)
+                    for (int q = threadIdx.x; q < L2::ACAP; q += T)
+                        for (int a = 0; a < 4; ++a)
+                            l2.acc()[a][q] = 0.0;
+                const Moves mv = g2p_item<R, SH, T, SHARED>(S, s.item, parts<R>(S, (int)s.cur), node_buf<R>(S, buf),
+                                                            node_buf<R>(S, buf ^ 1), t, l2, red,
+                                                            (int64_t)s.steps + k + 1);
+                if (mv.err)
+                    atomicOr(&S.ctl[CTL_ERR], mv.err);
+                if (mv.lost)
+                    atomicAdd(&S.ctl[CTL_LOST], mv.lost);
+                if (mv.drift)
+                    set_live(&S.ctl[CTL_NEED_SORT], 1u);
+                ev = ev || mv.err || mv.drift;
+                if (threadIdx.x == 0) {
+                    kept.tile[buf ^ 1] = mv.box;
+                    pick(S.tiles, buf ^ 1)[s.it] = mv.box;
+                }
+                __syncthreads();
+            });
+            event = barrier_wait(bar, ev, &sh);
+        }
+        if (event)
+            barrier_wait<true>(bar, false, &sh);   // the particles, before others take them up
+    }
+    if (!bar.ok)
+        for (int s = threadIdx.x; s < B.nscenes; s += blockDim.x)
+            atomicOr(&B.ctls[s][CTL_ERR], (uint32_t)ERR_SORT);
+    // the last workgroup leaves the words clear for the next launch
+    if (threadIdx.x == 0)
+        sh[0] = atomicAdd(&B.flags[BF_STEP_EXIT], 1u) + 1u == gridDim.x ? 1u : 0u;
+    __syncthreads();
+    if (sh[0])
+        for (int w = threadIdx.x; w < BF_WORDS; w += blockDim.x)
+            B.flags[w] = 0u;
 }
 
 // USL: particle velocity and position, then the strain increment from the
@@ -3978,6 +4572,7 @@ static KernelSet make_set()
     k.nodes_out = (const void *)&k_nodes_out<R>;
     k.reorder = (const void *)&k_reorder<R>;
     k.sort_move = (const void *)&k_sort_move<R>;
+    k.steps = (const void *)&k_steps<R, SH, kStepThreads>;
     set_items<R, SH, 0>(k);
     set_items<R, SH, 1>(k);
     set_items<R, SH, 2>(k);

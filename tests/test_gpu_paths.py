@@ -135,3 +135,121 @@ def test_isoparametric_location_of_fast_particles(ctx, mp, algo, prec):
     s.step(3)
     check(f"iso-fast/{algo}/{prec}", s.read(), oracle.run(sc, 3), sc["x"], BARS[prec])
     s.destroy()
+
+
+def _flying(seed, v, n_cells=(9, 7, 6), shape=0, vel=2.0):
+    sc = scenes.random_block(n_cells=n_cells, mesh_cells=(24, 20, 14), seed=seed, vel=vel, dt=1e-4, stress_scale=2e3,
+                             shape=shape, material=scenes.drucker_prager(psi_deg=5, c=1e3),
+                             bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE))
+    sc["x"] = sc["x"] + np.array([-0.1, 0.05, 0.1])
+    sc["v"] = sc["v"] + np.asarray(v, dtype=np.float64)
+    return sc
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["linear", "gimp", "iso", "pic"])
+def test_steps_in_one_launch_on_uneven_batches(ctx, mp, kind, prec):
+    """Batches small enough for all their steps to run in one launch: scenes of
+    1 to 14 items that end after different steps (none, one, ...), some fast
+    enough to reorder several times on the way, over three calls."""
+    shape = 1 if kind == "gimp" else 0
+    big = [(5, 4, 3), (6, 5, 3)] if kind == "iso" else [(9, 7, 6), (12, 8, 7)]   # the oracle's location is slow
+    scs = [_flying(80, (150.0, -60.0, 40.0), big[0], shape), _flying(81, (0.0, 0.0, 0.0), (4, 3, 3), shape),
+           _flying(82, (-30.0, 10.0, 90.0), big[1], shape), _flying(83, (5.0, 0.0, 0.0), (1, 1, 1), shape)]
+    if kind == "pic":
+        for sc in scs:
+            sc["scheme"]["velocity_update"] = scenes.PIC
+    if kind == "iso":
+        scs = [scenes.distort(sc, amp=0.2, seed=84) for sc in scs]
+    ss = [ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32) for sc in scs]
+    calls = [[12, 3, 7, 1], [9, 0, 13, 2], [4, 17, 0, 20]]
+    for call in calls:
+        ctx.batch_step(ss, call)
+    for i, (sc, s) in enumerate(zip(scs, ss)):
+        k = sum(c[i] for c in calls)
+        st = s.stats()
+        assert st["error_bits"] == 0 and st["steps_done"] == k, (i, st)
+        if i == 0:
+            assert 2 <= st["n_sorts"] < k, st
+        check(f"steps/{kind}/{prec}/{i}", s.read(), oracle.run(sc, k), sc["x"], BARS[prec])
+        s.destroy()
+
+
+def test_steps_in_one_launch_stop_at_an_error(ctx, mp):
+    """A scene that leaves the mesh stops there, as the one-step calls stop
+    it; the others of its batch go on."""
+    scs = [_flying(85, (0.0, 0.0, 500.0)), _flying(86, (0.0, 0.0, 0.0)), _flying(87, (60.0, 0.0, 0.0))]
+    one = ctx.create_scene(scs[0], precision=mp.FP64)
+    for _ in range(40):
+        one.step(1)
+    want = one.stats()
+    ss = [ctx.create_scene(sc, precision=mp.FP64) for sc in scs]
+    ctx.batch_step(ss, [40, 40, 25])
+    st = ss[0].stats()
+    assert st["error_bits"] == want["error_bits"] == mp.ERRBIT_OUT_OF_MESH, (st, want)
+    assert 0 < st["steps_done"] == want["steps_done"] < 40, (st, want)
+    for i, k in ((1, 40), (2, 25)):
+        assert ss[i].stats()["steps_done"] == k
+        check(f"steps-error/{i}", ss[i].read(), oracle.run(scs[i], k), scs[i]["x"], BARS["fp64"])
+    for s in [one] + ss:
+        s.destroy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_steps_in_one_launch_with_many_items_per_workgroup(ctx, mp, prec):
+    """A sparse cloud that expands from 216 bricks to over 2500, so that a
+    workgroup's items outgrow what it keeps of them from step to step."""
+    sc = scenes.random_block(n_cells=(23, 23, 23), mesh_cells=(72, 72, 72), seed=5, vel=0.2, dt=1e-4,
+                             gravity=(0.0, 0.0, 0.0), bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE),
+                             material=scenes.elastic(E=1e3), jitter=0.3)
+    pick = np.random.default_rng(5).permutation(len(sc["x"]))[::8]
+    sc.update({k: np.ascontiguousarray(sc[k][pick]) for k in ("x", "v", "stress", "vol", "mass")})
+    h = sc["mesh"]["h"]
+    sc["x"] = sc["x"] + np.array([0.0, 0.0, 24 * h])
+    sc["v"] = sc["v"] + 500.0 * (sc["x"] - 36 * h)
+    s = ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32)
+    s.step(30)
+    st = s.stats()
+    assert st["error_bits"] == 0 and st["n_sorts"] >= 2 and st["n_items"] > 8 * 256, st
+    check(f"steps-many-items/{prec}", s.read(), oracle.run(sc, 30), sc["x"], BARS[prec])
+    s.destroy()
+
+
+def test_steps_in_more_launches_than_one(ctx, mp):
+    """More steps in a call than one launch takes (1024), at rest under
+    gravity on a fixed floor."""
+    sc = scenes.random_block(n_cells=(3, 2, 2), mesh_cells=(9, 8, 6), seed=88, vel=0.1)
+    s = ctx.create_scene(sc, precision=mp.FP64)
+    s.step(2100)
+    assert s.stats()["steps_done"] == 2100
+    check("steps-launches", s.read(), oracle.run(sc, 2100), sc["x"], BARS["fp64"])
+    s.destroy()
+
+
+def test_steps_in_one_launch_from_two_threads(mp):
+    """Two contexts, each with a thread and a stream of its own, step batches
+    that both ask for most of the device: neither waits for the other's
+    workgroups to end, and both are right."""
+    import threading
+    sc = scenes.random_block(n_cells=(23, 22, 23), mesh_cells=(40, 40, 40), seed=89, vel=0.5, stress_scale=1e3)
+    ref = oracle.run(sc, 60)
+    out = [None, None]
+
+    def work(i):
+        c = mp.Context(0)
+        s = c.create_scene(sc, precision=mp.FP64)
+        for _ in range(3):
+            s.step(20)
+        out[i] = (s.read(), s.stats())
+        s.destroy()
+        c.close()
+
+    th = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    for i in range(2):
+        got, st = out[i]
+        assert st["error_bits"] == 0 and st["steps_done"] == 60, st
+        check(f"steps-threads/{i}", got, ref, sc["x"], BARS["fp64"])
