@@ -203,6 +203,7 @@ struct mpmx_ctx {
     hipStream_t capture = nullptr;         // private stream for graph capture
     hipStream_t launch_stream = nullptr;   // stream of the launches being issued
     DevicePool pool;
+    uint8_t *pinned = nullptr;             // kPinnedBytes of pinned host memory (see its layout)
     void *staging = nullptr;               // device staging of host inputs/outputs
     uint64_t staging_cap = 0;
     // mpmx_batch_step_noalloc: this device's address of the file-scope
@@ -494,6 +495,17 @@ void free_scene(mpmx_ctx *ctx, Scene *s)
     ctx->pool.release(s->block);
     s->block = nullptr;
 }
+
+// The context's pinned host memory: a scene's control words as the device
+// reports them, the image of a new scene's control words and descriptor, and
+// small particle arrays on their way in or out.  Only one call uses it at a
+// time, and each waits for the device before it returns.  A blocking copy
+// from or to ordinary host memory costs 10 to 20 us however small, a queued
+// one 2 us; arrays of more than kPinnedBytes go there and back directly,
+// where the copies' own rate decides.
+constexpr uint64_t kPinnedImage = 256, kPinnedArrays = 4096, kPinnedBytes = kPinnedArrays + (1u << 20);
+static_assert(kPinnedImage + 256 + sizeof(SceneDev) <= kPinnedArrays, "the scene image fits");
+static_assert(4 * CTL_WORDS <= 256, "the control words fit their slot");
 
 // Device staging area of at least `bytes` (contents not preserved); every
 // user synchronises the stream before returning.
@@ -1054,6 +1066,13 @@ int mpmx_create(mpmx_ctx **out, int device, void *stream)
         return MPMX_E_HIP;
     }
     ctx->scratch = sp;
+    if (hipHostMalloc((void **)&ctx->pinned, kPinnedBytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipStreamDestroy(ctx->aux);
+        if (ctx->own_stream)
+            (void)hipStreamDestroy(ctx->stream);
+        delete ctx;
+        return MPMX_E_OOM;
+    }
     ctx->scratch_img.assign(40 * (size_t)kNoAllocMaxScenes + 16, 0);
     *out = ctx;
     return MPMX_OK;
@@ -1076,6 +1095,7 @@ void mpmx_destroy(mpmx_ctx *ctx)
     ctx->fences.clear();
     if (ctx->staging)
         (void)hipFree(ctx->staging);
+    (void)hipHostFree(ctx->pinned);
     ctx->pool.clear();
     for (auto &pe : ctx->prof.pending) {
         (void)hipEventDestroy(pe.a);
@@ -1280,7 +1300,10 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
             return nullptr;
         void *p = (uint8_t *)s->block + used;
         used += align_up(bytes);
-        if (zero)
+        if (zero && !zero_ranges.empty() &&
+            (uint8_t *)zero_ranges.back().first + zero_ranges.back().second == (uint8_t *)p)
+            zero_ranges.back().second += align_up(bytes);
+        else if (zero)
             zero_ranges.push_back({p, align_up(bytes)});
         return p;
     };
@@ -1363,11 +1386,8 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
     for (auto &z : zero_ranges)
         if (ok && hipMemsetAsync(z.first, 0, z.second, ctx->aux) != hipSuccess)
             ok = false;
-    // the control words below are written with blocking copies: the zeroing
-    // must be complete first
-    if (ok && hipStreamSynchronize(ctx->aux) != hipSuccess)
-        ok = false;
     if (!ok) {
+        (void)hipStreamSynchronize(ctx->aux);
         free_scene(ctx, s);
         return fail(ctx, MPMX_E_OOM, "device arrays of %llu bytes do not fit the scene's block",
                     (unsigned long long)total);
@@ -1426,13 +1446,17 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
         if (!stage)
             ok = false;
         uint64_t soff = 0;
+        const bool small = align_up(24 * np) * 2 + align_up(48 * np) + 2 * align_up(8 * np) <=
+                           kPinnedBytes - kPinnedArrays;
         auto up = [&](const double *src, size_t count) -> const double * {
             if (!src || !ok)
                 return nullptr;
             void *p = stage + soff;
-            soff += align_up(count * 8);
-            if (hipMemcpy(p, src, count * 8, hipMemcpyHostToDevice) != hipSuccess)
+            if (small)
+                std::memcpy(ctx->pinned + kPinnedArrays + soff, src, count * 8);
+            else if (hipMemcpy(p, src, count * 8, hipMemcpyHostToDevice) != hipSuccess)
                 ok = false;
+            soff += align_up(count * 8);
             return (const double *)p;
         };
         dx = up(parts->x, 3 * np);
@@ -1440,6 +1464,9 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
         dsig = up(parts->stress, 6 * np);
         dvol = up(parts->vol, np);
         dmass = up(parts->mass, np);
+        if (ok && small &&
+            hipMemcpyAsync(stage, ctx->pinned + kPinnedArrays, soff, hipMemcpyHostToDevice, ctx->aux) != hipSuccess)
+            ok = false;
     } else if (np > 0) {
         std::vector<double> m(np);
         if (hipMemcpy(m.data(), parts->mass, 8 * np, hipMemcpyDeviceToHost) != hipSuccess)
@@ -1461,14 +1488,18 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
     h.f_etab = (float)h.etab;
     h.f_apex = (float)h.apex_p;
     h.f_inv_hard = (float)h.inv_hard;
-    uint32_t ctl[CTL_WORDS] = {0};
+    // the control words and the descriptor, which follow each other in the
+    // scene's block, and after the load the control words again, in the order
+    // of the second stream
+    uint32_t *ctl = (uint32_t *)(ctx->pinned + kPinnedImage);
+    std::memset(ctl, 0, 4 * CTL_WORDS);
     ctl[CTL_NEED_SORT] = 1;
     ctl[CTL_ALGO] = (uint32_t)h.algo;
     for (int a = 0; a < 3; ++a)
         ctl[CTL_LOW + a] = (uint32_t)std::numeric_limits<int>::max();
-    if (ok && hipMemcpy(h.ctl, ctl, sizeof ctl, hipMemcpyHostToDevice) != hipSuccess)
-        ok = false;
-    if (ok && hipMemcpy(s->d, &h, sizeof(SceneDev), hipMemcpyHostToDevice) != hipSuccess)
+    const uint64_t after = (uint64_t)((uint8_t *)s->d - (uint8_t *)h.ctl);
+    std::memcpy(ctx->pinned + kPinnedImage + after, &h, sizeof(SceneDev));
+    if (ok && hipMemcpyAsync(h.ctl, ctl, after + sizeof(SceneDev), hipMemcpyHostToDevice, ctx->aux) != hipSuccess)
         ok = false;
     if (ok && np > 0) {
         const KernelSet &K = kernel_set(s->prec, s->shape);
@@ -1477,15 +1508,14 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
         if (hipLaunchKernel(K.load, particle_grid(np), dim3(kLoadThreads), args, 0, ctx->aux) != hipSuccess)
             ok = false;
     }
-    if (ok && hipStreamSynchronize(ctx->aux) != hipSuccess)
+    ctl = (uint32_t *)ctx->pinned;
+    if (ok && hipMemcpyAsync(ctl, h.ctl, 4 * CTL_WORDS, hipMemcpyDeviceToHost, ctx->aux) != hipSuccess)
+        ok = false;
+    if (hipStreamSynchronize(ctx->aux) != hipSuccess)
         ok = false;
     if (!ok) {
         free_scene(ctx, s);
         return fail(ctx, MPMX_E_HIP, "scene upload failed");
-    }
-    if (hipMemcpy(ctl, h.ctl, sizeof ctl, hipMemcpyDeviceToHost) != hipSuccess) {
-        free_scene(ctx, s);
-        return fail(ctx, MPMX_E_HIP, "scene status read failed");
     }
     if (ctl[CTL_ERR]) {
         free_scene(ctx, s);
@@ -1690,48 +1720,53 @@ int mpmx_scene_read(mpmx_ctx *ctx, uint64_t scene, const mpmx_particles_out *out
     if (rc)
         return rc;
     const int64_t np = s->h.np;
+    uint32_t *ctl = (uint32_t *)ctx->pinned;
+    bool ok = true;
     if (np > 0) {
-        double *x = out->x, *v = out->v, *sg = out->stress, *vol = out->vol;
-        int32_t *cell = out->cell;
+        // host outputs are staged through device memory, and small ones
+        // through pinned memory from there, in one copy
+        void *host[5] = {out->x, out->v, out->stress, out->vol, out->cell}, *dst[5];
+        const uint64_t bytes[5] = {24 * (uint64_t)np, 24 * (uint64_t)np, 48 * (uint64_t)np, 8 * (uint64_t)np,
+                                   4 * (uint64_t)np};
+        const bool to_host = out->mem == MPMX_MEM_HOST;
+        uint64_t off[5], total = 0;
+        for (int f = 0; f < 5; ++f) {
+            off[f] = total;
+            if (host[f])
+                total += align_up(bytes[f]);
+        }
         uint8_t *stage = nullptr;
-        if (out->mem == MPMX_MEM_HOST)
-            stage = (uint8_t *)staging(ctx, 2 * align_up(24 * np) + align_up(48 * np) + align_up(8 * np) +
-                                                align_up(4 * np));
-        uint64_t soff = 0;
-        auto dev = [&](void *host, size_t bytes) -> void * {
-            if (!host || out->mem == MPMX_MEM_DEVICE)
-                return host;
-            if (!stage)
-                return nullptr;
-            void *p = stage + soff;
-            soff += align_up(bytes);
-            return p;
-        };
-        double *dx = (double *)dev(x, 24 * np), *dv = (double *)dev(v, 24 * np);
-        double *ds = (double *)dev(sg, 48 * np), *dvo = (double *)dev(vol, 8 * np);
-        int32_t *dc = (int32_t *)dev(cell, 4 * np);
-        bool ok = (!x || dx) && (!v || dv) && (!sg || ds) && (!vol || dvo) && (!cell || dc);
+        if (to_host && total && !(stage = (uint8_t *)staging(ctx, total)))
+            return fail(ctx, MPMX_E_HIP, "particle read failed");
+        for (int f = 0; f < 5; ++f)
+            dst[f] = !host[f] || !to_host ? host[f] : stage + off[f];
+        const bool small = total <= kPinnedBytes - kPinnedArrays;
         const KernelSet &K = kernel_set(s->prec, s->shape);
         SceneDev *d = s->d;
-        void *args[] = {&d, &dx, &dv, &ds, &dvo, &dc};
+        void *args[] = {&d, &dst[0], &dst[1], &dst[2], &dst[3], &dst[4], &ctl};
         const dim3 rg((unsigned)std::min<int64_t>(ceil_div(np, kReadParticles), 1 << 20));
-        if (ok && hipLaunchKernel(K.read_out, rg, dim3(kReadThreads), args, 0, ctx->aux) != hipSuccess)
+        if (hipLaunchKernel(K.read_out, rg, dim3(kReadThreads), args, 0, ctx->aux) != hipSuccess)
             ok = false;
-        if (ok && hipStreamSynchronize(ctx->aux) != hipSuccess)
+        if (ok && to_host && total && small &&
+            hipMemcpyAsync(ctx->pinned + kPinnedArrays, stage, total, hipMemcpyDeviceToHost, ctx->aux) != hipSuccess)
             ok = false;
-        if (ok && out->mem == MPMX_MEM_HOST) {
-            if (x && hipMemcpy(x, dx, 24 * np, hipMemcpyDeviceToHost) != hipSuccess) ok = false;
-            if (v && hipMemcpy(v, dv, 24 * np, hipMemcpyDeviceToHost) != hipSuccess) ok = false;
-            if (sg && hipMemcpy(sg, ds, 48 * np, hipMemcpyDeviceToHost) != hipSuccess) ok = false;
-            if (vol && hipMemcpy(vol, dvo, 8 * np, hipMemcpyDeviceToHost) != hipSuccess) ok = false;
-            if (cell && hipMemcpy(cell, dc, 4 * np, hipMemcpyDeviceToHost) != hipSuccess) ok = false;
+        if (hipStreamSynchronize(ctx->aux) != hipSuccess)
+            ok = false;
+        for (int f = 0; f < 5; ++f) {
+            if (!ok || !to_host || !host[f])
+                continue;
+            if (small)
+                std::memcpy(host[f], ctx->pinned + kPinnedArrays + off[f], bytes[f]);
+            else if (hipMemcpy(host[f], dst[f], bytes[f], hipMemcpyDeviceToHost) != hipSuccess)
+                ok = false;
         }
-        if (!ok)
-            return fail(ctx, MPMX_E_HIP, "particle read failed");
+    } else {
+        ok = hipMemcpyAsync(ctl, s->h.ctl, 4 * CTL_WORDS, hipMemcpyDeviceToHost, ctx->aux) == hipSuccess;
+        if (hipStreamSynchronize(ctx->aux) != hipSuccess)
+            ok = false;
     }
-    HIPCHK(ctx, hipStreamSynchronize(ctx->aux));
-    uint32_t ctl[CTL_WORDS];
-    HIPCHK(ctx, hipMemcpy(ctl, s->h.ctl, sizeof(uint32_t) * CTL_WORDS, hipMemcpyDeviceToHost));
+    if (!ok)
+        return fail(ctx, MPMX_E_HIP, "particle read failed");
     if (ctl[CTL_ERR])
         return fail(ctx, err_code(ctl[CTL_ERR]), "scene stopped on error bits %u", ctl[CTL_ERR]);
     return MPMX_OK;

@@ -1298,8 +1298,9 @@ __device__ inline void store_rows(T *out, const T *lds, const uint32_t *pid, int
     }
 }
 
-// Particle state in original order (row-major doubles); any pointer may be
-// null.  One workgroup takes kReadParticles consecutive particles (a full
+// Particle state in original order (row-major doubles); any pointer of the
+// arrays may be null.  The scene's control words go to ctl (host memory), in
+// place of a copy of their own.  One workgroup takes kReadParticles consecutive particles (a full
 // brick's), loads their fields at once and stores them one by one through
 // LDS.  Storing each particle's words from its own lane left 8-byte pieces of
 // cache lines that two XCDs' L2s completed in part: 25.2M particles 3229 ->
@@ -1307,7 +1308,7 @@ __device__ inline void store_rows(T *out, const T *lds, const uint32_t *pid, int
 // KB per workgroup and took 1560 and 113 us).
 template <typename R>
 __global__ void __launch_bounds__(kReadThreads)
-    k_read_out(const SceneDev *Sd, double *x, double *v, double *sig, double *vol, int32_t *cell)
+    k_read_out(const SceneDev *Sd, double *x, double *v, double *sig, double *vol, int32_t *cell, uint32_t *ctl)
 {
     constexpr int U = kReadParticles / kReadThreads;
     __shared__ double rows[6 * (kReadParticles + kReadParticles / 64)];
@@ -1315,6 +1316,8 @@ __global__ void __launch_bounds__(kReadThreads)
     const SceneDev &S = *Sd;
     const int64_t n = S.np;
     const int cur = (int)cld(&S.ctl[CTL_CUR]);
+    if (blockIdx.x == 0 && threadIdx.x < CTL_WORDS)
+        ctl[threadIdx.x] = S.ctl[threadIdx.x];
     const double *X = S.x[cur];
     const R *V = (const R *)S.v[cur];
     const R *SG = (const R *)S.sig[cur];

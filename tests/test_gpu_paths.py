@@ -253,3 +253,22 @@ def test_steps_in_one_launch_from_two_threads(mp):
         got, st = out[i]
         assert st["error_bits"] == 0 and st["steps_done"] == 60, st
         check(f"steps-threads/{i}", got, ref, sc["x"], BARS["fp64"])
+
+
+@pytest.mark.parametrize("n", [9300, 9361, 9362, 9363, 9707, 9708, 9709, 9800])
+def test_host_arrays_around_the_pinned_memory_size(ctx, mp, n):
+    """Scenes whose host arrays just fit, or do not fit, 1 MiB (112 bytes a
+    particle on the way in, 108 on the way out): every value comes back, from
+    two scenes in turn."""
+    sc = scenes.random_block(n_cells=(11, 11, 11), mesh_cells=(22, 16, 14), seed=90, vel=0.3, stress_scale=2e3)
+    rng = np.random.default_rng(n)
+    scs = []
+    for _ in range(2):
+        pick = rng.permutation(len(sc["x"]))[:n]
+        scs.append(dict(sc, **{k: np.ascontiguousarray(sc[k][pick]) for k in ("x", "v", "stress", "vol", "mass")}))
+    ss = [ctx.create_scene(c, precision=mp.FP64) for c in scs]
+    for c, s in zip(scs, ss):
+        got = s.read()
+        for k in ("x", "v", "stress", "vol"):
+            np.testing.assert_array_equal(got[k], c[k], err_msg=k)
+        s.destroy()
