@@ -656,7 +656,13 @@ __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int 
 // requires.  Only slots 2 mix two translates: 16.7 cycles per add on the
 // same layout (1806 per 64 particles), with 27/64 of the anchored form's
 // arithmetic.  It suits the force scatter, whose anchored form is
-// VALU-bound; two particles of one cell cannot share its adds.
+// VALU-bound, and a particle by itself.  Two particles of one cell cannot
+// share its adds: for the mass and momentum of such a pair the anchored form
+// stays the cheaper one (1060 cycles a particle).  Single particles rotated
+// instead of anchored, per step: 393k particles at random places in their
+// cells 83.6 -> 67.2 us (USL 79.8 -> 66.9, MUSL 125 -> 107), 51200 in
+// k_steps, which knows no pairs, 27.9 -> 23.8; bodies of regular layout,
+// whose particles mostly pair up, as before.
 constexpr int kAnchPX = 12, kAnchPXY = 108, kAnchCap = 972;   // 12 x 9 x 9 entries
 
 // The 4 anchored weights (and their derivatives) of one axis from a 3-node
@@ -2271,10 +2277,11 @@ __device__ inline Parts<R> parts(const SceneDev &S, int cur)
 // into the node box t, flushed to node buffer nb; with force, a second pass
 // of the nodal force (internal from the current stress and volume, and
 // gravity) through the same LDS accumulators.  When the box fits the
-// anchored layout (kAnchPX), each particle adds its mass and momentum to the
-// 4 x 4 x 4 anchored slots of its cell, a thread's two particles in one cell
-// (successive particles of the cell in level-major order) sharing one set of
-// adds, and its force to its 27 support nodes in rotated order; otherwise
+// anchored layout (kAnchPX), a thread's two particles in one cell (successive
+// particles of the cell in level-major order) add their mass and momentum to
+// the 4 x 4 x 4 anchored slots of the cell in one set of adds; a particle by
+// itself, and every particle's force, goes to its 27 support nodes in rotated
+// order.  Otherwise
 // each particle adds to its 27-node support at the box's pitches.
 template <typename R, bool WITH_FORCE, int T>
 __device__ __attribute__((always_inline)) inline void p2g_gimp_item(const SceneDev &S, const Parts<R> &P, const NodeBuf<R> &nb, const Item &item,
@@ -2321,7 +2328,7 @@ __device__ __attribute__((always_inline)) inline void p2g_gimp_item(const SceneD
             for (int a = 0; a < 3; ++a)
                 mv[u][a] = m[u] * ldg(P.v[a], p);
         }
-        if (anch) {
+        if (anch && rb >= 0) {
             const int a0 = entry(c[0] - 1, c[1] - 1, c[2] - 1);
             for (int k = 0; k < 4; ++k)
                 for (int j = 0; j < 4; ++j) {
@@ -2342,6 +2349,30 @@ __device__ __attribute__((always_inline)) inline void p2g_gimp_item(const SceneD
                         atomicAdd(&acc[1][li], (double)s0);
                         atomicAdd(&acc[2][li], (double)s1);
                         atomicAdd(&acc[3][li], (double)s2);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
+                }
+        } else if (anch) {
+            // a particle by itself: its 27 nodes in rotated order
+            const Support<R, 1> &sp = sq[0];
+            R wr[3][3], unused[3];
+            int e[3];
+            for (int a = 0; a < 3; ++a)
+                e[a] = rotate3<R>(sp.w[a], sp.dw[a], sp.base[a] == c[a], wr[a], unused);
+            const int a0 = entry(c[0] - 1, c[1] - 1, c[2] - 1);
+            const int ox[3] = {1, 2, e[0]}, oy[3] = {kAnchPX, 2 * kAnchPX, kAnchPX * e[1]},
+                      oz[3] = {kAnchPXY, 2 * kAnchPXY, kAnchPXY * e[2]};
+            for (int k = 0; k < 3; ++k)
+                for (int j = 0; j < 3; ++j) {
+                    const R wyz = wr[1][j] * wr[2][k];
+                    const int row = a0 + oy[j] + oz[k];
+                    for (int i = 0; i < 3; ++i) {
+                        const R N = wr[0][i] * wyz;
+                        const int li = row + ox[i];
+                        atomicAdd(&acc[0][li], (double)(N * m[0]));
+                        atomicAdd(&acc[1][li], (double)(N * mv[0][0]));
+                        atomicAdd(&acc[2][li], (double)(N * mv[0][1]));
+                        atomicAdd(&acc[3][li], (double)(N * mv[0][2]));
                     }
                     __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
                 }
@@ -3143,18 +3174,22 @@ __device__ __attribute__((always_inline)) inline Moves g2p_item(const SceneDev &
     auto scatter = [&](const Support<R, SH> &sq, const int cq[3], bool inh, R m, const R mvq[3]) {
         const Corners hq = corners(S, ht, sq.base);
         if (SH == 1 && inh) {
-            // anchored 4 x 4 x 4 slots (see kAnchPX); home-tile coordinates
-            // of node c - 1 are c - o + 1 in [0, 5] for a cell in the home region
-            R w4[3][4], dw4[3][4];
+            // the 27 support nodes in rotated order (see kAnchPX); home-tile
+            // coordinates of node c - 1 are c - o + 1 in [0, 5] for a cell in
+            // the home region
+            R wr[3][3], unused[3];
+            int e[3];
             for (int a = 0; a < 3; ++a)
-                anchor4<R>(sq.w[a], sq.dw[a], sq.base[a] == cq[a] ? 1 : 0, w4[a], dw4[a]);
+                e[a] = rotate3<R>(sq.w[a], sq.dw[a], sq.base[a] == cq[a], wr[a], unused);
             const int a0 = (cq[0] - 1 - ht.lo[0]) + APX * (cq[1] - 1 - ht.lo[1]) + APXY * (cq[2] - 1 - ht.lo[2]);
-            for (int k = 0; k < 4; ++k)
-                for (int j = 0; j < 4; ++j) {
-                    const R wyz = w4[1][j] * w4[2][k];
-                    for (int i = 0; i < 4; ++i) {
-                        const R N = w4[0][i] * wyz;
-                        const int li = a0 + i + APX * j + APXY * k;
+            const int ox[3] = {1, 2, e[0]}, oy[3] = {APX, 2 * APX, APX * e[1]}, oz[3] = {APXY, 2 * APXY, APXY * e[2]};
+            for (int k = 0; k < 3; ++k)
+                for (int j = 0; j < 3; ++j) {
+                    const R wyz = wr[1][j] * wr[2][k];
+                    const int rb = a0 + oy[j] + oz[k];
+                    for (int i = 0; i < 3; ++i) {
+                        const R N = wr[0][i] * wyz;
+                        const int li = rb + ox[i];
                         atomicAdd(&acc[0][li], (double)(N * m));
                         atomicAdd(&acc[1][li], (double)(N * mvq[0]));
                         atomicAdd(&acc[2][li], (double)(N * mvq[1]));
@@ -3529,7 +3564,7 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 // A step is bound by the chain of latencies of one item's two stages (about
 // 5 us each) and two barriers.  512 threads, one particle each, keep that
 // chain shortest (no loop over particles).  Measured per step against the
-// separate kernels: 1000 particles 18.9 -> 14.6 us (GIMP 29.1 -> 24.4, FP64
+// separate kernels: 1000 particles 18.9 -> 14.6 us (GIMP 29.1 -> 20.5, FP64
 // 18.9 -> 16.7, isoparametric 25.1 -> 20.0), 51200 particles 22.0 -> 16.8 us.
 
 constexpr uint64_t kStartTicks = 10000ull;       // 100 us of the 100 MHz wall clock
@@ -4216,7 +4251,7 @@ __device__ __attribute__((always_inline)) inline void musl_g2p_gimp_item(const S
             for (int a = 0; a < 3; ++a)
                 anchor4<R>(sq[u].w[a], sq[u].dw[a], sq[u].base[a] == c[a] ? 1 : 0, w4[u][a], unused);
         }
-        if (anch) {
+        if (anch && rb >= 0) {
             const int a0 = entry(c[0] - 1, c[1] - 1, c[2] - 1);
             for (int k = 0; k < 4; ++k)
                 for (int j = 0; j < 4; ++j) {
@@ -4236,6 +4271,29 @@ __device__ __attribute__((always_inline)) inline void musl_g2p_gimp_item(const S
                         atomicAdd(&acc[0][li], (double)s0);
                         atomicAdd(&acc[1][li], (double)s1);
                         atomicAdd(&acc[2][li], (double)s2);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
+                }
+        } else if (anch) {
+            // a particle by itself: its 27 nodes in rotated order
+            const Support<R, 1> &sp = sq[0];
+            R wr[3][3], unused[3];
+            int e[3];
+            for (int a = 0; a < 3; ++a)
+                e[a] = rotate3<R>(sp.w[a], sp.dw[a], sp.base[a] == c[a], wr[a], unused);
+            const int a0 = entry(c[0] - 1, c[1] - 1, c[2] - 1);
+            const int ox[3] = {1, 2, e[0]}, oy[3] = {kAnchPX, 2 * kAnchPX, kAnchPX * e[1]},
+                      oz[3] = {kAnchPXY, 2 * kAnchPXY, kAnchPXY * e[2]};
+            for (int k = 0; k < 3; ++k)
+                for (int j = 0; j < 3; ++j) {
+                    const R wyz = wr[1][j] * wr[2][k];
+                    const int row = a0 + oy[j] + oz[k];
+                    for (int i = 0; i < 3; ++i) {
+                        const R N = wr[0][i] * wyz;
+                        const int li = row + ox[i];
+                        atomicAdd(&acc[0][li], (double)(N * mvs[ra][0]));
+                        atomicAdd(&acc[1][li], (double)(N * mvs[ra][1]));
+                        atomicAdd(&acc[2][li], (double)(N * mvs[ra][2]));
                     }
                     __builtin_amdgcn_sched_barrier(0);   // one row of LDS adds in flight
                 }

@@ -272,3 +272,25 @@ def test_host_arrays_around_the_pinned_memory_size(ctx, mp, n):
         for k in ("x", "v", "stress", "vol"):
             np.testing.assert_array_equal(got[k], c[k], err_msg=k)
         s.destroy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("algo", [scenes.USF, scenes.USL, scenes.MUSL])
+def test_gimp_particles_alone_and_in_pairs(ctx, mp, algo, prec):
+    """Cells of one to eight particles at random places: a thread's two
+    particles share a cell or do not, through the separate kernels (the
+    allocation-free call) and the default path."""
+    sc = scenes.random_block(n_cells=(9, 6, 5), mesh_cells=(18, 13, 11), shape=1, seed=91, vel=0.5, stress_scale=2e3,
+                             material=scenes.drucker_prager(psi_deg=5, c=1e3))
+    sc["scheme"]["algo"] = algo
+    h = sc["mesh"]["h"]
+    rng = np.random.default_rng(91)
+    keep = rng.random(len(sc["x"])) < 0.6
+    sc.update({k: np.ascontiguousarray(sc[k][keep]) for k in ("x", "v", "stress", "vol", "mass")})
+    sc["x"] = (np.floor(sc["x"] / h) + rng.uniform(0.02, 0.98, size=sc["x"].shape)) * h
+    ref = oracle.run(sc, 4)
+    for noalloc in (False, True):
+        s = ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32)
+        (ctx.batch_step_noalloc if noalloc else ctx.batch_step)([s], [4])
+        check(f"gimp-pairs/{algo}/{prec}/{noalloc}", s.read(), ref, sc["x"], BARS[prec])
+        s.destroy()
