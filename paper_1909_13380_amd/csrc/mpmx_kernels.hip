@@ -3834,9 +3834,12 @@ struct Slot {
 constexpr int kSlots = 8;   // items a workgroup keeps; with more it loads them again for every stage
 
 // Slots of items id + (base + m) n, m < kSlots, below total, with the boxes
-// recorded last.
+// recorded last.  The first barrier: a slot whose scene has finished is left
+// out without one, so another wavefront may still read the slots to be
+// overwritten.
 __device__ inline void load_slots(const BatchDev &B, const Team &b, uint32_t base, uint32_t total, Slot *slots)
 {
+    __syncthreads();
     const uint32_t m = threadIdx.x, g = b.id + (base + m) * b.n;
     if (m < (uint32_t)kSlots && g < total) {
         auto get = [](const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };

@@ -294,3 +294,28 @@ def test_gimp_particles_alone_and_in_pairs(ctx, mp, algo, prec):
         (ctx.batch_step_noalloc if noalloc else ctx.batch_step)([s], [4])
         check(f"gimp-pairs/{algo}/{prec}/{noalloc}", s.read(), ref, sc["x"], BARS[prec])
         s.destroy()
+
+
+def test_steps_in_one_launch_of_scenes_that_end_with_many_items_left(ctx, mp):
+    """Clouds that spread to over 2400 bricks each in one batch, then a call in
+    which they end after different steps: a workgroup reloads the items it
+    keeps several times a stage, with finished scenes' items among them."""
+    scs = []
+    for seed in range(92, 98):
+        sc = scenes.random_block(n_cells=(11, 11, 11), mesh_cells=(72, 72, 72), seed=seed, vel=0.2, dt=1e-4,
+                                 gravity=(0.0, 0.0, 0.0), bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE),
+                                 material=scenes.elastic(E=1e3), jitter=0.3)
+        mid = 36 * sc["mesh"]["h"]
+        sc["x"] = sc["x"] - 0.5 * (sc["x"].min(0) + sc["x"].max(0)) + mid
+        sc["v"] = sc["v"] + 400.0 * (sc["x"] - mid)
+        scs.append(sc)
+    ss = [ctx.create_scene(sc, precision=mp.FP64) for sc in scs]
+    calls = [[112] * 6, [3, 14, 1, 9, 6, 12]]
+    for call in calls:
+        ctx.batch_step(ss, call)
+    for i, (sc, s) in enumerate(zip(scs, ss)):
+        k = sum(c[i] for c in calls)
+        st = s.stats()
+        assert st["error_bits"] == 0 and st["steps_done"] == k and st["n_items"] > 2400, (i, st)
+        check(f"steps-uneven-many/{i}", s.read(), oracle.run(sc, k), sc["x"], BARS["fp64"])
+        s.destroy()
