@@ -724,12 +724,20 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 // step slower, not wrong.  Calls of fewer than three steps have nothing to
 // share; profiled, always-sorting and fixed-shape (no autotuning or graphs)
 // calls keep one launch per kernel.
-constexpr int64_t kStepsPerLaunch = 1024;
+//
+// A reorder inside the launch reads every brick's counters with half the
+// wavefronts of the reorder kernel.  Per reorder (4096 particles, us), in its
+// own kernel and in k_steps: 1000 bricks 75, 73; 65536 bricks 105, 100;
+// 262144 bricks 130, 154; 1048576 bricks 257, 375.  Per step of a body that
+// moves 0.1 cells a step, 262144 bricks 36.1, 34.8 (0.3 cells 55.4, 57.7);
+// 1048576 bricks 47.0, 54.7.  So meshes of more than kStepsBricks bricks keep
+// one launch per kernel.
+constexpr int64_t kStepsPerLaunch = 1024, kStepsBricks = 1 << 18;
 
 bool steps_at_once(const mpmx_ctx *ctx, const Batch &b)
 {
     return ctx->autotune && ctx->graph_steps > 0 && !ctx->prof.on && b.algo == MPMX_USF && !b.always &&
-           b.items <= ctx->num_cu;
+           b.items <= ctx->num_cu && b.bd.total_bricks <= kStepsBricks;
 }
 
 int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)

@@ -166,7 +166,8 @@ enum BatchFlag : int {
     // what goes with it (barriers passed and events; 64-bit) and the steps
     // left; the barrier's arrivals of groups (and events; 64-bit) and per
     // group; the release word (barriers and events; 64-bit) polled by group
-    // g; workgroups finished
+    // g; workgroups finished; the last barrier after which a workgroup of XCD
+    // x wrote back its L2
     BF_STEP_START = BF_EXIT,
     BF_STEP_LIST = BF_CLAIM,
     BF_STEP_INFO = BF_CLAIM + 2,
@@ -174,6 +175,7 @@ enum BatchFlag : int {
     BF_STEP_EXIT = BF_CLAIM + 34,
     BF_STEP_ROOT = BF_CLAIM + 32,
     BF_STEP_GROUP = BF_CLAIM + 64,      // + 32 g
+    BF_STEP_WRITER = BF_STEP_GROUP + 1, // + 32 (x mod 8) + x div 8
     BF_STEP_RELEASE = BF_RELEASE        // + 32 g
 };
 

@@ -319,3 +319,55 @@ def test_steps_in_one_launch_of_scenes_that_end_with_many_items_left(ctx, mp):
         assert st["error_bits"] == 0 and st["steps_done"] == k and st["n_items"] > 2400, (i, st)
         check(f"steps-uneven-many/{i}", s.read(), oracle.run(sc, k), sc["x"], BARS["fp64"])
         s.destroy()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("mesh", [(40, 36, 24), (76, 72, 60), (100, 90, 80)])
+def test_reorders_inside_a_launch_on_large_meshes(ctx, mp, mesh, prec):
+    """Small fast bodies on meshes of 500 to 13000 bricks, stepped together:
+    a few, some or many workgroups share each reorder."""
+    scs = []
+    for seed, v in ((101, (150.0, -50.0, 30.0)), (102, (-90.0, 60.0, 20.0))):
+        sc = scenes.random_block(n_cells=(6, 5, 5), mesh_cells=mesh, seed=seed, vel=2.0, dt=1e-4, stress_scale=2e3,
+                                 material=scenes.drucker_prager(psi_deg=5, c=1e3),
+                                 bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE))
+        sc["x"] = sc["x"] + np.array([0.0, 0.0, 0.2])
+        sc["v"] = sc["v"] + np.asarray(v)
+        scs.append(sc)
+    ss = [ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32) for sc in scs]
+    ctx.batch_step(ss, [40, 33])
+    for i, (sc, s, k) in enumerate(zip(scs, ss, (40, 33))):
+        st = s.stats()
+        assert st["error_bits"] == 0 and st["steps_done"] == k and st["n_sorts"] >= 4, (i, st)
+        check(f"reorders-large/{mesh}/{prec}/{i}", s.read(), oracle.run(sc, k), sc["x"], BARS[prec])
+        s.destroy()
+
+
+def test_reorders_inside_a_launch_use_the_device(ctx, mp):
+    """A small body that reorders every few steps on a mesh of 65536 bricks:
+    a step costs about 2.5 times that of the body at rest (reorders by one
+    workgroup made it 65 times, separate kernels 2.2 times); 10 leaves room
+    for a busy machine."""
+    import time
+    import torch
+    t = []
+    for vx in (0.0, 150.0):
+        sc = scenes.random_block(n_cells=(8, 8, 8), mesh_cells=(256, 128, 128), seed=7, vel=0.01, dt=1e-4,
+                                 gravity=(0.0, 0.0, 0.0), bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE))
+        sc["x"] = sc["x"] + np.array([0.0, 0.0, 0.2])
+        sc["v"] = sc["v"] + np.array([vx, 0.3 * vx, 0.2 * vx])
+        s = ctx.create_scene(sc, precision=mp.FP32)
+        s.step(40)
+        best = np.inf
+        for _ in range(3):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            s.step(40)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+        st = s.stats()
+        assert st["error_bits"] == 0 and (st["n_sorts"] > 20) == (vx > 0), st
+        t.append(best)
+        s.destroy()
+    print(f"[reorders-device] per step at rest {t[0] / 40e-6:.1f} us, moving {t[1] / 40e-6:.1f} us", flush=True)
+    assert t[1] < 10 * t[0], t
