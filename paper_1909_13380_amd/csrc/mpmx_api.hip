@@ -79,7 +79,7 @@ struct Batch {
     BatchDev bd{};
     int prec = 0, shape = 0, algo = 0;
     bool always = false;    // some scene reorders after every step
-    int64_t items = 0;      // sum of the scenes' items
+    int64_t items = 0;      // sum of the items of the scenes that the present call steps
     // the last queued steps of this batch (its image is free to rewrite
     // once they are done)
     std::shared_ptr<StepEvent> last_use;
@@ -173,7 +173,7 @@ struct Scene {
     std::shared_ptr<StepEvent> last;
     bool main_sync = false;
     bool fresh = true;       // no steps queued yet: its first step reorders
-    int64_t items = 0;       // work items of the particles as loaded (estimate)
+    int64_t items = 0;       // work items: of the particles as loaded (estimate), later as last reported
 };
 
 }  // namespace
@@ -184,6 +184,7 @@ struct mpmx_ctx {
     bool own_stream = false;
     int num_cu = 256;
     int reorder_per_cu[2] = {0, 0};   // by precision; 0 until first queried
+    int wide_per_cu[2][3] = {};       // k_steps' wide shape, by precision and kernel shape; likewise
     std::string err;
     uint64_t next_id = 1;
     std::map<uint64_t, std::unique_ptr<Scene>> scenes;
@@ -548,7 +549,7 @@ int build_batch(mpmx_ctx *ctx, Batch &b, const std::vector<Scene *> &list)
                  o_co = o_io + 4 * n1, o_fl = (o_co + 4 * n1 + 127) & ~(size_t)127, o_sc = o_fl + 4 * BF_WORDS,
                  o_br = o_sc + 16 * (size_t)kScanChunks, total = o_br + 4 * (size_t)std::max<int64_t>(nbr, 1);
     std::vector<uint8_t> img(total, 0);
-    int64_t maxit = 0, items = 0, *po = (int64_t *)(img.data() + o_po), *bo = (int64_t *)(img.data() + o_bo);
+    int64_t maxit = 0, *po = (int64_t *)(img.data() + o_po), *bo = (int64_t *)(img.data() + o_bo);
     SceneDev **sp = (SceneDev **)img.data();
     uint32_t **cp = (uint32_t **)(img.data() + o_ct);
     for (int i = 0; i < n; ++i) {
@@ -557,9 +558,7 @@ int build_batch(mpmx_ctx *ctx, Batch &b, const std::vector<Scene *> &list)
         po[i + 1] = po[i] + list[i]->h.np;
         bo[i + 1] = bo[i] + list[i]->h.nbricks;
         maxit += list[i]->h.max_items;
-        items += list[i]->items;
     }
-    b.items = items;
     b.always = std::any_of(list.begin(), list.end(), [](const Scene *sc) { return sc->h.sort_always != 0; });
     if (total > b.dcap) {
         if (b.dmem)
@@ -719,20 +718,32 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 //   110592, 216 items 22.2, 18.1; 147456, 288 items 23.8, 30.0;
 //   262144, 512 items 29.0, 32.2.
 // Beyond one item per workgroup the separate kernels win, with several
-// smaller workgroups resident on each compute unit.  The host knows the
-// particles' extent as loaded; items that a spreading body adds later make a
-// step slower, not wrong.  Calls of fewer than three steps have nothing to
-// share; profiled, always-sorting and fixed-shape (no autotuning or graphs)
-// calls keep one launch per kernel.
+// smaller workgroups resident on each compute unit.  The host knows the items
+// as last reported to it (until then, the bricks of the extent as loaded).  A
+// body that spreads over more of them within a call leaves the launch, and
+// the call's remaining steps run in launches of the wide shape (128 threads,
+// kWidePerCu workgroups per compute unit), which are queued behind it and
+// return at once (2 us) where it was not left.  Per step, over the whole call,
+// in separate kernels, with the one shape only, and with both (us): 85184
+// particles that spread from 216 to 729 items 30.0, 39.5, 29.3, to 2744 items
+// 46.0, 69.8, 49.0; 10648 particles to 2924 items 38.0, 57.7, 40.6 (GIMP 58.8,
+// 86.9, 55.3); 12167 particles to 3114 items with a reorder every other step
+// 62.5, 94, 73.  The wide shape at 2, 3, 4 and 6 per compute unit: 44.3, 40.6,
+// 41.5, 42.1 (10648 particles).
+//
+// Calls of fewer than three steps have nothing to share; profiled,
+// always-sorting and fixed-shape (no autotuning or graphs) calls keep one
+// launch per kernel.
 //
 // A reorder inside the launch reads every brick's counters with half the
 // wavefronts of the reorder kernel.  Per reorder (4096 particles, us), in its
-// own kernel and in k_steps: 1000 bricks 75, 73; 65536 bricks 105, 100;
-// 262144 bricks 130, 154; 1048576 bricks 257, 375.  Per step of a body that
-// moves 0.1 cells a step, 262144 bricks 36.1, 34.8 (0.3 cells 55.4, 57.7);
-// 1048576 bricks 47.0, 54.7.  So meshes of more than kStepsBricks bricks keep
+// own kernel and in k_steps: 1331 bricks 75, 73; 70785 bricks 105, 100;
+// 274625 bricks 130, 154; 1081665 bricks 257, 375.  Per step of a body that
+// moves 0.1 cells a step, 274625 bricks 36.1, 34.8 (0.3 cells 55.4, 57.7);
+// 1081665 bricks 47.0, 54.7.  So meshes of more than kStepsBricks bricks keep
 // one launch per kernel.
-constexpr int64_t kStepsPerLaunch = 1024, kStepsBricks = 1 << 18;
+constexpr int64_t kStepsPerLaunch = 1024, kWideStepsPerLaunch = 128, kStepsBricks = 1 << 18;
+constexpr int kWidePerCu = 3;
 
 bool steps_at_once(const mpmx_ctx *ctx, const Batch &b)
 {
@@ -744,15 +755,31 @@ int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)
 {
     const KernelSet &K = kernel_set(b.prec, b.shape);
     BatchDev bd = b.bd;
-    const dim3 grid((unsigned)std::clamp<int64_t>(bd.max_items, 1, ctx->num_cu)), t(kStepThreads);
-    while (left > 0) {
-        uint32_t n = (uint32_t)std::min(left, kStepsPerLaunch);
-        void *args[] = {&bd, &n};
-        if (int rc = launch(ctx, "steps", K.steps, grid, t, args))
-            return rc;
-        left -= n;
+    const uint32_t cus = (uint32_t)ctx->num_cu;
+    auto queue = [&](const void *fn, int threads, int per_cu, int64_t per_launch, uint32_t limit) {
+        const dim3 grid((unsigned)std::clamp<int64_t>(bd.max_items, 1, (int64_t)per_cu * cus));
+        for (int64_t todo = left; todo > 0;) {
+            uint32_t n = (uint32_t)std::min(todo, per_launch);
+            void *args[] = {&bd, &n, &limit};
+            if (int rc = launch(ctx, "steps", fn, grid, dim3(threads), args))
+                return rc;
+            todo -= n;
+        }
+        return (int)MPMX_OK;
+    };
+    if (int rc = queue(K.steps, kStepThreads, 1, kStepsPerLaunch, cus))
+        return rc;
+    if (bd.max_items <= cus)   // never more items than that
+        return MPMX_OK;
+    int &per_cu = ctx->wide_per_cu[b.prec ? 1 : 0][b.shape];
+    if (per_cu == 0) {
+        int occ = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, K.steps_wide, kStepWideThreads, 0) != hipSuccess ||
+            occ < 1)
+            occ = 1;
+        per_cu = std::min(occ, kWidePerCu);
     }
-    return MPMX_OK;
+    return queue(K.steps_wide, kStepWideThreads, per_cu, kWideStepsPerLaunch, 0u);
 }
 
 uint64_t layout_key(const Batch &b)
@@ -963,12 +990,14 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
         }
     }
     bool fresh = false;
+    b.items = 0;
     for (int i = 0; i < n; ++i) {
         Scene *s = ns[i] > 0 ? find(ctx, b.ids[i]) : nullptr;
-        if (s && s->fresh) {
-            fresh = true;
-            s->fresh = false;
-        }
+        if (!s)
+            continue;
+        fresh = fresh || s->fresh;
+        s->fresh = false;
+        b.items += s->items;
     }
     if ((rc = enqueue_step(ctx, b, cfg, true, fresh || b.always, nullptr)))
         return rc;
@@ -1004,10 +1033,19 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
     return mark_queued(ctx, b);
 }
 
+// The scene's items as its control words, read back, report them (a scene
+// that has not been reordered yet has none).
+void note_items(Scene *s, const uint32_t *ctl)
+{
+    if (ctl[CTL_N_SORTS] > 0)
+        s->items = ctl[CTL_N_ITEMS];
+}
+
 int read_ctl(mpmx_ctx *ctx, Scene *s, uint32_t *ctl)
 {
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     HIPCHK(ctx, hipMemcpy(ctl, s->h.ctl, sizeof(uint32_t) * CTL_WORDS, hipMemcpyDeviceToHost));
+    note_items(s, ctl);
     return MPMX_OK;
 }
 
@@ -1775,6 +1813,7 @@ int mpmx_scene_read(mpmx_ctx *ctx, uint64_t scene, const mpmx_particles_out *out
     }
     if (!ok)
         return fail(ctx, MPMX_E_HIP, "particle read failed");
+    note_items(s, ctl);
     if (ctl[CTL_ERR])
         return fail(ctx, err_code(ctl[CTL_ERR]), "scene stopped on error bits %u", ctl[CTL_ERR]);
     return MPMX_OK;

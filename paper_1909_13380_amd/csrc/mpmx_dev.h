@@ -30,6 +30,7 @@ constexpr int kBlock = 1024;              // threads per workgroup of the reorde
 constexpr int kSortThreads = 256;         // threads per workgroup of the reorder phases launched one by one
 constexpr int kSortBricks = 32;           // fewest bricks per workgroup of their scan
 constexpr int kStepThreads = 512;         // threads per workgroup of k_steps: one particle each
+constexpr int kStepWideThreads = 128;     // the same while a batch has more items than compute units
 constexpr int kSortU = 4;                 // particles per lane in flight in the reorder's particle phases
 constexpr int kLoadThreads = 256;         // threads per workgroup of the particle load
 constexpr int kReadThreads = 256;         // threads per workgroup of the particle read
@@ -167,7 +168,9 @@ enum BatchFlag : int {
     // left; the barrier's arrivals of groups (and events; 64-bit) and per
     // group; the release word (barriers and events; 64-bit) polled by group
     // g; workgroups finished; the last barrier after which a workgroup of XCD
-    // x wrote back its L2
+    // x wrote back its L2; and, for the launches queued behind it, whether a
+    // launch was left for more items than its shape suits
+    BF_STEP_MORE = 2,
     BF_STEP_START = BF_EXIT,
     BF_STEP_LIST = BF_CLAIM,
     BF_STEP_INFO = BF_CLAIM + 2,

@@ -3555,9 +3555,9 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 // keep busy run the phases, with fences after each, and the first one
 // publishes the steps' list after them.  Per step of a body that moves 0.3
 // cells a step (a reorder every four), in the separate kernels, with the
-// whole reorder on the first workgroup, and shared: 1000 particles on 6144
+// whole reorder on the first workgroup, and shared: 1000 particles on 7225
 // bricks 38.7, 134, 33.6 us; 51200 particles 57.5, 298, 51.0; 4096 particles
-// on 65536 bricks 49.0, 1113, 43.5.
+// on 70785 bricks 49.0, 1113, 43.5.
 //
 // A barrier completes only if every workgroup it counts is running, and other
 // kernels may hold part of the device for any time (other launches of this
@@ -3940,14 +3940,17 @@ __device__ inline Slot uni_slot(const Slot &s)
 
 // Up to `left` steps of every scene of the batch.  On entry one step of the
 // call has run: node buffer CTL_NBUF holds its data and the other one the
-// next step's mass and momentum.
+// next step's mass and momentum.  A batch that comes to more than `limit`
+// items leaves the launch for the ones queued behind it in the other launch
+// shape (limit = 0), which do nothing unless it does.
 template <typename R, int SH, int T>
-__global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left)
+__global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left, uint32_t limit)
 {
+    if (limit == 0u && live(&B.flags[BF_STEP_MORE]) == 0u)
+        return;
     using L1 = StressLds<R, SH>;
     using L2 = G2pLds<R, SH>;
     constexpr int KP = kChunk / T;
-    static_assert(KP == 1, "one particle per thread");
     // the two stages' arrays, and the control's, share LDS
     constexpr int BYTES = (int)sizeof(L1) > L2::BYTES ? (int)sizeof(L1) : L2::BYTES;
     static_assert(BYTES >= T * (int)sizeof(Seg), "the control's scans fit");
@@ -3975,7 +3978,10 @@ __global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left)
                 publish_list(bar, (uint32_t)min(most, (int64_t)gridDim.x), true);
             } else {
                 const uint32_t items = steps_items(B, raw);
-                publish_list(bar, items == 0u || bar.left == 0u ? 0u : gridDim.x, false);
+                const bool leave = limit != 0u && items > limit;
+                if (leave && threadIdx.x == 0)
+                    set_live(&B.flags[BF_STEP_MORE], 1u);
+                publish_list(bar, items == 0u || bar.left == 0u || leave ? 0u : gridDim.x, false);
             }
         }
         if (!take_list(bar, &sh))
@@ -4010,7 +4016,9 @@ __global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left)
                 const int buf = (int)((s.nbuf ^ 1u ^ k) & 1u);
                 const Parts<R> P = parts<R>(S, (int)s.cur);
                 uint32_t pcell[KP];
-                pcell[0] = ldg(P.cell, s.item.start + min((uint32_t)threadIdx.x, s.item.count - 1u));
+#pragma unroll
+                for (int rr = 0; rr < KP; ++rr)
+                    pcell[rr] = ldg(P.cell, s.item.start + min((uint32_t)threadIdx.x + rr * T, s.item.count - 1u));
                 const NodeBuf<R> nb = node_buf<R>(S, buf), other = node_buf<R>(S, buf ^ 1);
                 Tile t;
                 if (k > 0) {
@@ -4029,6 +4037,14 @@ __global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left)
                     unpack_cell(pcell[0], mn);
                     for (int a = 0; a < 3; ++a)
                         mx[a] = mn[a];
+                    for (int rr = 1; rr < KP; ++rr) {
+                        int c[3];
+                        unpack_cell(pcell[rr], c);
+                        for (int a = 0; a < 3; ++a) {
+                            mn[a] = min(mn[a], c[a]);
+                            mx[a] = max(mx[a], c[a]);
+                        }
+                    }
                     item_box<T>(mn, mx, red, lo, hi);
                     t = tile_of_cells<SH>(lo, hi);
                     if (threadIdx.x == 0) {
@@ -4080,13 +4096,15 @@ __global__ void __launch_bounds__(T) k_steps(BatchDev B, uint32_t left)
     if (!bar.ok)
         for (int s = threadIdx.x; s < B.nscenes; s += blockDim.x)
             atomicOr(&B.ctls[s][CTL_ERR], (uint32_t)ERR_SORT);
-    // the last workgroup leaves the words clear for the next launch
+    // the last workgroup leaves the words clear for the next launch, but for
+    // the one that the launches behind this one read
     if (threadIdx.x == 0)
         sh[0] = atomicAdd(&B.flags[BF_STEP_EXIT], 1u) + 1u == gridDim.x ? 1u : 0u;
     __syncthreads();
     if (sh[0])
         for (int w = threadIdx.x; w < BF_WORDS; w += blockDim.x)
-            B.flags[w] = 0u;
+            if (w != BF_STEP_MORE)
+                B.flags[w] = 0u;
 }
 
 // USL: particle velocity and position, then the strain increment from the
@@ -4710,6 +4728,7 @@ static KernelSet make_set()
     k.reorder = (const void *)&k_reorder<R>;
     k.sort_move = (const void *)&k_sort_move<R>;
     k.steps = (const void *)&k_steps<R, SH, kStepThreads>;
+    k.steps_wide = (const void *)&k_steps<R, SH, kStepWideThreads>;
     set_items<R, SH, 0>(k);
     set_items<R, SH, 1>(k);
     set_items<R, SH, 2>(k);

@@ -16,7 +16,8 @@ struct KernelSet {
     const void *read_out;   // (const SceneDev*, x, v, sig, vol, cell, ctl)
     const void *nodes_out;  // (const SceneDev*, m, p, f)
     const void *reorder;    // (BatchDev): reorder, then the step control
-    const void *steps;      // (BatchDev, steps): many USF steps in one launch (small batches)
+    const void *steps;      // (BatchDev, steps, items): many USF steps in one launch (small batches)
+    const void *steps_wide; // the same, in smaller workgroups, several per compute unit
     const void *sort_move;  // (BatchDev): the reorder's last phase as a launch of its own
     const void *p2g[kNumItemThreadChoices];      // (BatchDev)
     const void *stress[kNumItemThreadChoices];   // (BatchDev)

@@ -371,3 +371,100 @@ def test_reorders_inside_a_launch_use_the_device(ctx, mp):
         s.destroy()
     print(f"[reorders-device] per step at rest {t[0] / 40e-6:.1f} us, moving {t[1] / 40e-6:.1f} us", flush=True)
     assert t[1] < 10 * t[0], t
+
+
+def _spreading(seed=92):
+    """10648 particles on 27 bricks that spread over more than 2000."""
+    sc = scenes.random_block(n_cells=(11, 11, 11), mesh_cells=(72, 72, 72), seed=seed, vel=0.2, dt=1e-4,
+                             gravity=(0.0, 0.0, 0.0), bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE),
+                             material=scenes.elastic(E=1e3), jitter=0.3)
+    mid = 36 * sc["mesh"]["h"]
+    sc["x"] = sc["x"] - 0.5 * (sc["x"].min(0) + sc["x"].max(0)) + mid
+    sc["v"] = sc["v"] + 400.0 * (sc["x"] - mid)
+    return sc
+
+
+def test_a_body_that_has_spread_returns_to_the_separate_kernels(mp):
+    """The items that a read reports decide how the next call runs: a body
+    that has spread over more than one per compute unit goes back to graphs
+    of the separate kernels."""
+    sc = _spreading()
+    c = mp.Context(0)
+    try:
+        s = c.create_scene(sc, precision=mp.FP64)
+        s.step(100)
+        assert c.get_option(mp.OPT_GRAPH_LAUNCHES) == 0
+        s.read()
+        s.step(17)
+        assert c.get_option(mp.OPT_GRAPH_LAUNCHES) == 2
+        assert s.stats()["n_items"] > 2000
+        check("spread-read", s.read(), oracle.run(sc, 117), sc["x"], BARS["fp64"])
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind", ["linear", "gimp", "iso", "slow"])
+def test_a_body_that_spreads_within_a_call(ctx, mp, kind, prec):
+    """The launch is left within the call, for the wide shape, whose steps
+    take more than one launch where the body spreads slowly; scenes that
+    spread little or end early go along.  The oracle's location is slow on a
+    mesh of this size, so the isoparametric scenes are held against the
+    separate kernels (the allocation-free call)."""
+    scs = [_spreading(104), scenes.random_block(n_cells=(3, 3, 2), seed=105, vel=0.2, dt=1e-4, gravity=(0.0, 0.0, 0.0),
+                                                material=scenes.elastic(E=1e3)),
+           scenes.random_block(n_cells=(4, 4, 4), seed=106, vel=0.2, dt=1e-4, gravity=(0.0, 0.0, 0.0),
+                               material=scenes.elastic(E=1e3))]
+    if kind == "iso":
+        scs = [scenes.distort(sc, amp=0.1, seed=107) for sc in scs]
+    for sc in scs:
+        sc["scheme"]["shape"] = scenes.SHAPE_GIMP if kind == "gimp" else scenes.SHAPE_LINEAR
+    k = [110, 90, 110]
+    if kind == "slow":
+        scs[0]["v"] = 0.5 * scs[0]["v"]
+        k = [225, 90, 225]
+    ss = [ctx.create_scene(sc, precision=mp.FP64 if prec == "fp64" else mp.FP32) for sc in scs]
+    ctx.batch_step(ss, k)
+    if kind == "iso":
+        other = [ctx.create_scene(sc, precision=mp.FP64) for sc in scs]
+        ctx.batch_step_noalloc(other, k)
+        refs = [s.read() for s in other]
+        for s in other:
+            s.destroy()
+    else:
+        refs = [oracle.run(sc, n) for sc, n in zip(scs, k)]
+    for i, (sc, s, ref) in enumerate(zip(scs, ss, refs)):
+        st = s.stats()
+        assert st["error_bits"] == 0 and st["steps_done"] == k[i], (i, st)
+        assert i or st["n_items"] > 2000, st
+        check(f"spread-call/{kind}/{prec}/{i}", s.read(), ref, sc["x"], BARS[prec])
+        s.destroy()
+
+
+def test_a_body_that_spreads_costs_little_more_than_in_separate_kernels(mp):
+    """100 steps in one call of a body that spreads from 27 to over 2000
+    bricks, against the separate kernels: 1.1 times their time (7 times with
+    one launch shape and reorders by one workgroup); 3 leaves room for a busy
+    machine."""
+    import time
+    import torch
+    sc = _spreading()
+    t = []
+    for auto in (1, 0):
+        c = mp.Context(0)
+        c.set_option(mp.OPT_AUTOTUNE, auto)
+        best = np.inf
+        for _ in range(4):
+            s = c.create_scene(sc, precision=mp.FP32)
+            s.step(1)
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            s.step(100)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+            assert s.stats()["error_bits"] == 0
+            s.destroy()
+        t.append(best)
+        c.close()
+    print(f"[spread-time] per step {t[0] * 1e4:.1f} us, separate kernels {t[1] * 1e4:.1f} us", flush=True)
+    assert t[0] < 3 * t[1], t
