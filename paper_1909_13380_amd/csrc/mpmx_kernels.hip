@@ -506,17 +506,29 @@ __device__ inline void iso_point(const IsoCell &k, const double r[3], double x[3
                k.b[5][a] * rt + k.b[6][a] * rst;
 }
 
-// (dx/dr)^-1 at r in FP32, the step matrix of the location iteration.
-__device__ inline void iso_step_matrix(const IsoCell &k, const double rd[3], float Mi[3][3])
+// A place in an isoparametric cell: local coordinates r, and the step matrix
+// Mi that located them: (dx/dr)^-1 in FP32 at a point within `off` (maximum
+// norm) of r.
+struct IsoAt {
+    double r[3];
+    float Mi[3][3];
+    float off;
+};
+
+// The step matrix at the place itself.
+__device__ inline void iso_step_matrix(const IsoCell &k, IsoAt &at)
 {
-    const float r[3] = {(float)rd[0], (float)rd[1], (float)rd[2]};
+    const float r[3] = {(float)at.r[0], (float)at.r[1], (float)at.r[2]};
     const float rs = r[0] * r[1], st = r[1] * r[2], rt = r[0] * r[2];
     float M[3][3];
+    float(&Mi)[3][3] = at.Mi;
     for (int a = 0; a < 3; ++a) {
-        const float b3 = (float)k.b[3][a], b4 = (float)k.b[4][a], b5 = (float)k.b[5][a], b6 = (float)k.b[6][a];
-        M[a][0] = (float)k.b[0][a] + b3 * r[1] + b5 * r[2] + b6 * st;
-        M[a][1] = (float)k.b[1][a] + b3 * r[0] + b4 * r[2] + b6 * rt;
-        M[a][2] = (float)k.b[2][a] + b4 * r[1] + b5 * r[0] + b6 * rs;
+        float b[7];
+        for (int q = 0; q < 7; ++q)
+            b[q] = (float)k.b[q][a];
+        M[a][0] = b[0] + b[3] * r[1] + b[5] * r[2] + b[6] * st;
+        M[a][1] = b[1] + b[3] * r[0] + b[4] * r[2] + b[6] * rt;
+        M[a][2] = b[2] + b[4] * r[1] + b[5] * r[0] + b[6] * rs;
     }
     const float c00 = M[1][1] * M[2][2] - M[1][2] * M[2][1];
     const float c01 = M[1][2] * M[2][0] - M[1][0] * M[2][2];
@@ -533,63 +545,81 @@ __device__ inline void iso_step_matrix(const IsoCell &k, const double rd[3], flo
     Mi[2][2] = (M[0][0] * M[1][1] - M[0][1] * M[1][0]) * id;
 }
 
-// Local coordinates r of the point o + y in the cell, refined from r with the
-// step matrix Mi of a point near it.  The residual x(r) - y is FP64, the step
-// Mi (x(r) - y) FP32: what the step matrix lacks in accuracy (its rounding,
-// or that it belongs to a point nearby) only scales the error left by a step.
-// It is evaluated again (Newton-Raphson) while a step exceeds 1e-5; below
-// that, a step leaves at most about 2e-5 of itself, so the iteration ends
-// with a step of at most 1e-10, whose error is of the order of FP64 rounding.
-// A step costs 21 + 9 operations where Newton-Raphson in FP64 throughout cost
-// about 110 (1.05M particles: g2p_p2g 76.3 -> 61.3 us, stress 48.0 -> 44.9).
-// False if it broke down.
-__device__ inline bool iso_refine(const IsoCell &k, const double y[3], double r[3], float Mi[3][3])
+// One step of the location of the point o + y: at.r -= Mi (x(r) - y).
+// Returns the step's size.
+__device__ inline float iso_step(const IsoCell &k, const double y[3], IsoAt &at)
 {
-    for (int it = 0; it < 50; ++it) {
-        double x[3];
-        iso_point(k, r, x);
-        const float e[3] = {(float)(x[0] - y[0]), (float)(x[1] - y[1]), (float)(x[2] - y[2])};
-        float dmax = 0.0f;
-        for (int a = 0; a < 3; ++a) {
-            const float d = Mi[a][0] * e[0] + Mi[a][1] * e[1] + Mi[a][2] * e[2];
-            r[a] -= (double)d;
-            dmax = fmaxf(dmax, fabsf(d));
-        }
-        if (!(dmax > 1e-10f))   // converged, or not a number (the check below fails)
-            break;
-        if (dmax > 1e-5f)
-            iso_step_matrix(k, r, Mi);
+    double x[3];
+    iso_point(k, at.r, x);
+    const float e[3] = {(float)(x[0] - y[0]), (float)(x[1] - y[1]), (float)(x[2] - y[2])};
+    float dmax = 0.0f;
+    for (int a = 0; a < 3; ++a) {
+        const float d = at.Mi[a][0] * e[0] + at.Mi[a][1] * e[1] + at.Mi[a][2] * e[2];
+        at.r[a] -= (double)d;
+        dmax = fmaxf(dmax, fabsf(d));
     }
-    return isfinite(r[0]) && isfinite(r[1]) && isfinite(r[2]);
+    at.off += dmax;
+    return dmax;
+}
+
+// Refine the place of the point o + y.  The residual x(r) - y is FP64, the
+// step FP32: what the step matrix lacks in accuracy only scales the error that
+// a step leaves, to about `off` (it belongs to a point at that distance) plus
+// 1e-6 (its rounding) of the step.  The iteration ends where that is at most
+// 2e-16, FP64 rounding, and evaluates the matrix again (Newton-Raphson, the
+// price of one to two steps) where the next two steps would not end it.
+// Evaluated against extended precision over unit cells whose nodes are off by
+// up to 0.3: at most 1.3e-15 after moves of 0 to 0.05 of a cell, warm or cold
+// (stopping at a step of 1e-10 and evaluating the matrix only after steps
+// above 1e-5 left up to 9e-13 after a move of 0.01, and 6e-11 where the point
+// lies on an axis through the cell's centre, along which the residual vanishes
+// but the matrix changes).  A step costs 21 + 9 operations where
+// Newton-Raphson in FP64 throughout cost about 110 (1.05M particles: g2p_p2g
+// 76.3 -> 60.7 us, stress 48.0 -> 43.3; with the looser end 59.1 and 42.7).
+// 2: converged; 1: not within 50 steps; 0: broke down.
+__device__ inline int iso_refine(const IsoCell &k, const double y[3], IsoAt &at)
+{
+    int done = 1;
+    for (int it = 0; it < 50; ++it) {
+        const float d = iso_step(k, y, at);
+        if (!(d > 1e-10f) && !(d * at.off > 2e-16f)) {   // converged, or not a number (the check below fails)
+            done = 2;
+            break;
+        }
+        if (d * at.off * at.off * at.off > 1e-15f) {
+            iso_step_matrix(k, at);
+            at.off = 0.0f;
+        }
+    }
+    return isfinite(at.r[0]) && isfinite(at.r[1]) && isfinite(at.r[2]) ? done : 0;
 }
 
 // The same from the affine guess r0 = 1/2 + J(1/2)^-1 (y - x(1/2)), the
-// refinement's first step from the centre.
-__device__ inline bool iso_local(const IsoCell &k, const double y[3], double r[3], float Mi[3][3])
+// refinement's first step from the centre.  False if it broke down.
+__device__ inline bool iso_local(const IsoCell &k, const double y[3], IsoAt &at)
 {
-    r[0] = r[1] = r[2] = 0.5;
-    iso_step_matrix(k, r, Mi);
-    double x[3];
-    iso_point(k, r, x);
-    for (int a = 0; a < 3; ++a)
-        r[a] -= (double)(Mi[a][0] * (float)(x[0] - y[0]) + Mi[a][1] * (float)(x[1] - y[1]) +
-                         Mi[a][2] * (float)(x[2] - y[2]));
-    return iso_refine(k, y, r, Mi);
+    at.r[0] = at.r[1] = at.r[2] = 0.5;
+    iso_step_matrix(k, at);
+    at.off = 0.0f;
+    (void)iso_step(k, y, at);
+    return iso_refine(k, y, at) != 0;
 }
 
 // Cell of point x on an isoparametric mesh by a walk across cell faces from
 // cell c (updated in place; the particle's previous cell, or a first guess)
 // towards the point, at most `budget` cells: the cell whose local
 // coordinates of x lie in [0,1)^3 (the uniform mesh's half-open rule), its
-// geometry k and the local coordinates r.  With WARM, r is a guess in cell c
-// and Mi a step matrix near it (from the particle's previous position), and
-// the first cell starts from them.  A point that rounding leaves just past a face between two cells (by at most
-// 5e-13, never past the mesh's outer faces) goes to the one it overshoots
-// least.  Returns 0 or ERR_OUT_OF_MESH / ERR_NONFINITE.
+// geometry k and the place there.  With WARM, the place is a guess in cell c
+// (from the particle's previous position), from which the first cell starts;
+// it starts again from the centre where that does not converge.  A point that
+// rounding leaves just past a face between two cells (by at most 5e-13, never
+// past the mesh's outer faces) goes to the one it overshoots least.  Returns 0
+// or ERR_OUT_OF_MESH / ERR_NONFINITE.
 template <bool WARM>
-__device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int c[3], double r[3], IsoCell &k,
-                                      float Mi[3][3], int budget)
+__device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int c[3], IsoCell &k, IsoAt &at,
+                                      int budget)
 {
+    double(&r)[3] = at.r;
     if (!isfinite(x[0]) || !isfinite(x[1]) || !isfinite(x[2]))
         return ERR_NONFINITE;
     int best[3] = {-1, 0, 0}, prev[3] = {-1, -1, -1};
@@ -597,7 +627,8 @@ __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int 
     for (int m = 0; m < budget; ++m) {
         iso_cell(S, c, k);
         const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-        if (!(WARM && m == 0 ? iso_refine(k, y, r, Mi) : iso_local(k, y, r, Mi)))
+        const bool warm = WARM && m == 0 && iso_refine(k, y, at) == 2;
+        if (!warm && !iso_local(k, y, at))
             break;
         int d[3];
         bool in = true, outer = false;
@@ -761,10 +792,9 @@ __device__ inline void make_support(const SceneDev &S, const double x[3], const 
         IsoCell k;
         iso_cell(S, c, k);
         const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-        double r[3];
-        float Mi[3][3];
-        iso_local(k, y, r, Mi);
-        iso_support<R>(k, c, r, sp);
+        IsoAt at;
+        iso_local(k, y, at);
+        iso_support<R>(k, c, at.r, sp);
     } else if constexpr (SH == 0) {
         for (int a = 0; a < 3; ++a) {
             const R r = (R)((x[a] - (S.origin[a] + h * (double)c[a])) * ih);
@@ -789,13 +819,9 @@ __device__ inline void make_support(const SceneDev &S, const double x[3], const 
     }
 }
 
-// A particle's place in its isoparametric cell, kept from its support to the
-// location of its moved position.  The cell's geometry is loaded again there:
-// held across the gather, its 48 registers took g2p_p2g from 165 to 256.
-struct IsoAt {
-    double r[3];
-    float Mi[3][3];
-};
+// A particle's place is kept from its support to the location of its moved
+// position.  The cell's geometry is loaded again there: held across the
+// gather, its 48 registers took g2p_p2g from 165 to 256.
 
 // Support of a particle, keeping its place.
 template <typename R>
@@ -804,17 +830,23 @@ __device__ inline void iso_at(const SceneDev &S, const double x[3], const int c[
     IsoCell k;
     iso_cell(S, c, k);
     const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-    iso_local(k, y, at.r, at.Mi);
+    iso_local(k, y, at);
     iso_support<R>(k, c, at.r, sp);
 }
 
 // Cell nc (in: the old one) and place of a particle that moved by dx to x.
 __device__ inline uint32_t iso_moved(const SceneDev &S, const double x[3], const double dx[3], int nc[3], IsoAt &at)
 {
-    for (int a = 0; a < 3; ++a)
-        at.r[a] += (double)(at.Mi[a][0] * (float)dx[0] + at.Mi[a][1] * (float)dx[1] + at.Mi[a][2] * (float)dx[2]);
+    const float f[3] = {(float)dx[0], (float)dx[1], (float)dx[2]};
+    float far = 0.0f;
+    for (int a = 0; a < 3; ++a) {
+        const float d = at.Mi[a][0] * f[0] + at.Mi[a][1] * f[1] + at.Mi[a][2] * f[2];
+        at.r[a] += (double)d;
+        far = fmaxf(far, fabsf(d));
+    }
+    at.off += far;
     IsoCell k;
-    return iso_locate<true>(S, x, nc, at.r, k, at.Mi, kIsoWalk);
+    return iso_locate<true>(S, x, nc, k, at, kIsoWalk);
 }
 
 // --------------------------------------------------------- constitutive --
@@ -1230,10 +1262,9 @@ __global__ void __launch_bounds__(kLoadThreads) k_load(SceneDev *Sd, const doubl
                 const double q = floor((xp[a] - S.origin[a]) * S.inv_h);
                 c[a] = q < 0.0 ? 0 : (q >= (double)S.n[a] ? S.n[a] - 1 : (int)q);
             }
-            double r[3];
+            IsoAt at;
             IsoCell k;
-            float Mi[3][3];
-            e = iso_locate<false>(S, xp, c, r, k, Mi, S.n[0] + S.n[1] + S.n[2] + kIsoWalk);
+            e = iso_locate<false>(S, xp, c, k, at, S.n[0] + S.n[1] + S.n[2] + kIsoWalk);
         } else {
             e = locate(S, xp, c);
         }

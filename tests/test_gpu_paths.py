@@ -468,3 +468,61 @@ def test_a_body_that_spreads_costs_little_more_than_in_separate_kernels(mp):
         c.close()
     print(f"[spread-time] per step {t[0] * 1e4:.1f} us, separate kernels {t[1] * 1e4:.1f} us", flush=True)
     assert t[0] < 3 * t[1], t
+
+
+def _iso_body(seed, move):
+    """One particle in each cell of a block on a strongly distorted mesh, with
+    velocities that move it by up to `move` of a cell per step."""
+    h, dt = 0.05, 1e-4
+    sc = scenes.random_block(n_cells=(7, 7, 5), mesh_cells=(12, 11, 9), h=h, seed=seed, vel=move * h / dt, dt=dt,
+                             material=scenes.elastic(E=1e5), bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE))
+    sc["x"] = sc["x"] + np.array([0.0, 0.0, 2 * h])
+    sc.update({k: np.ascontiguousarray(sc[k][seed % 8::8]) for k in ("x", "v", "stress", "vol", "mass")})
+    return scenes.distort(sc, amp=0.3, seed=seed + 1)
+
+
+def _check_nodal_mass(mp, sc, steps):
+    """Nodal masses, sums of at most 8 particles' weights here, to 1e-14 of
+    the largest: the local coordinates on either side are good to 1.5e-15
+    (FP64 rounding), three axes to a weight."""
+    c = mp.Context(0)
+    try:
+        s = c.create_scene(sc, precision=mp.FP64)
+        s.step(steps)
+        got, ref = s.nodes()["m"], oracle.run(sc, steps)["grid"].m
+        err = np.max(np.abs(got - ref)) / np.max(ref)
+        print(f"[iso-mass] err {err:.2e}", flush=True)
+        assert err <= 1e-14, err
+    finally:
+        c.close()
+
+
+@pytest.mark.parametrize("move", [1e-6, 1e-3, 1e-2, 5e-2])
+def test_isoparametric_place_of_moved_particles_ends_at_rounding(mp, move):
+    """The second step's nodal masses, scattered from the place found for each
+    moved particle, whose iteration starts from its old place."""
+    for seed in (110, 112, 114):
+        _check_nodal_mass(mp, _iso_body(seed, move), 2)
+
+
+def test_isoparametric_place_on_a_cell_axis_ends_at_rounding(mp):
+    """Particles on the axes through their cells' centres, where the first
+    guess is exact along the axis but the step matrix is not."""
+    for seed in (116, 118, 120):
+        sc = _iso_body(seed, 0.0)
+        rng = np.random.default_rng(seed)
+        mesh, n = sc["mesh"], len(sc["x"])
+        X = np.asarray(mesh["node_x"]).reshape(mesh["n"][2] + 1, mesh["n"][1] + 1, mesh["n"][0] + 1, 3)
+        r = np.full((n, 3), 0.5)
+        r[np.arange(n), rng.integers(0, 3, n)] = rng.uniform(0.03, 0.97, n)
+        c = oracle.locate(mesh, sc["x"]).reshape(n, -1)
+        if c.shape[1] == 1:
+            c = np.stack([c[:, 0] % mesh["n"][0], c[:, 0] // mesh["n"][0] % mesh["n"][1],
+                          c[:, 0] // (mesh["n"][0] * mesh["n"][1])], axis=1)
+        x = np.zeros((n, 3))
+        for q in range(8):
+            o = np.array([q & 1, q >> 1 & 1, q >> 2])
+            i = c + o
+            x += np.prod(np.where(o, r, 1 - r), axis=1)[:, None] * X[i[:, 2], i[:, 1], i[:, 0]]
+        sc["x"] = x
+        _check_nodal_mass(mp, sc, 1)
