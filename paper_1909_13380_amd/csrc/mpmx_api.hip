@@ -1426,6 +1426,14 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
         if (ok)
             HIPCHK(ctx, hipMemcpy(dX, X.data(), 24 * sz.nn, hipMemcpyHostToDevice));
         h.X = (const double *)dX;
+        double edge = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const auto ends = std::minmax_element(X.begin() + a * sz.nn, X.begin() + (a + 1) * sz.nn);
+            edge = std::max(edge, *ends.second - *ends.first);
+        }
+        edge /= (double)std::max({mesh->n[0], mesh->n[1], mesh->n[2]});
+        const bool fine = edge > 0.0 && std::isfinite(edge);
+        h.iso_scale = fine ? std::ldexp(1.0f, std::clamp(-std::ilogb(edge), -120, 120)) : 1.0f;
     }
     // uploads go through the second stream, so that they overlap steps
     // already queued on the context stream

@@ -515,8 +515,10 @@ struct IsoAt {
     float off;
 };
 
-// The step matrix at the place itself.
-__device__ inline void iso_step_matrix(const IsoCell &k, IsoAt &at)
+// The step matrix at the place itself.  The scale s (SceneDev::iso_scale, a
+// power of two, so exact) is about one over the cells' edge: without it the
+// determinant leaves the range of FP32 for edges below 1e-13 or above 1e12.
+__device__ inline void iso_step_matrix(const IsoCell &k, float s, IsoAt &at)
 {
     const float r[3] = {(float)at.r[0], (float)at.r[1], (float)at.r[2]};
     const float rs = r[0] * r[1], st = r[1] * r[2], rt = r[0] * r[2];
@@ -526,14 +528,14 @@ __device__ inline void iso_step_matrix(const IsoCell &k, IsoAt &at)
         float b[7];
         for (int q = 0; q < 7; ++q)
             b[q] = (float)k.b[q][a];
-        M[a][0] = b[0] + b[3] * r[1] + b[5] * r[2] + b[6] * st;
-        M[a][1] = b[1] + b[3] * r[0] + b[4] * r[2] + b[6] * rt;
-        M[a][2] = b[2] + b[4] * r[1] + b[5] * r[0] + b[6] * rs;
+        M[a][0] = s * (b[0] + b[3] * r[1] + b[5] * r[2] + b[6] * st);
+        M[a][1] = s * (b[1] + b[3] * r[0] + b[4] * r[2] + b[6] * rt);
+        M[a][2] = s * (b[2] + b[4] * r[1] + b[5] * r[0] + b[6] * rs);
     }
     const float c00 = M[1][1] * M[2][2] - M[1][2] * M[2][1];
     const float c01 = M[1][2] * M[2][0] - M[1][0] * M[2][2];
     const float c02 = M[1][0] * M[2][1] - M[1][1] * M[2][0];
-    const float id = 1.0f / (M[0][0] * c00 + M[0][1] * c01 + M[0][2] * c02);
+    const float id = s * (1.0f / (M[0][0] * c00 + M[0][1] * c01 + M[0][2] * c02));
     Mi[0][0] = c00 * id;
     Mi[1][0] = c01 * id;
     Mi[2][0] = c02 * id;
@@ -577,7 +579,7 @@ __device__ inline float iso_step(const IsoCell &k, const double y[3], IsoAt &at)
 // Newton-Raphson in FP64 throughout cost about 110 (1.05M particles: g2p_p2g
 // 76.3 -> 60.7 us, stress 48.0 -> 43.3; with the looser end 59.1 and 42.7).
 // 2: converged; 1: not within 50 steps; 0: broke down.
-__device__ inline int iso_refine(const IsoCell &k, const double y[3], IsoAt &at)
+__device__ inline int iso_refine(const IsoCell &k, float s, const double y[3], IsoAt &at)
 {
     int done = 1;
     for (int it = 0; it < 50; ++it) {
@@ -587,7 +589,7 @@ __device__ inline int iso_refine(const IsoCell &k, const double y[3], IsoAt &at)
             break;
         }
         if (d * at.off * at.off * at.off > 1e-15f) {
-            iso_step_matrix(k, at);
+            iso_step_matrix(k, s, at);
             at.off = 0.0f;
         }
     }
@@ -596,13 +598,13 @@ __device__ inline int iso_refine(const IsoCell &k, const double y[3], IsoAt &at)
 
 // The same from the affine guess r0 = 1/2 + J(1/2)^-1 (y - x(1/2)), the
 // refinement's first step from the centre.  False if it broke down.
-__device__ inline bool iso_local(const IsoCell &k, const double y[3], IsoAt &at)
+__device__ inline bool iso_local(const IsoCell &k, float s, const double y[3], IsoAt &at)
 {
     at.r[0] = at.r[1] = at.r[2] = 0.5;
-    iso_step_matrix(k, at);
+    iso_step_matrix(k, s, at);
     at.off = 0.0f;
     (void)iso_step(k, y, at);
-    return iso_refine(k, y, at) != 0;
+    return iso_refine(k, s, y, at) != 0;
 }
 
 // Cell of point x on an isoparametric mesh by a walk across cell faces from
@@ -627,8 +629,8 @@ __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int 
     for (int m = 0; m < budget; ++m) {
         iso_cell(S, c, k);
         const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-        const bool warm = WARM && m == 0 && iso_refine(k, y, at) == 2;
-        if (!warm && !iso_local(k, y, at))
+        const bool warm = WARM && m == 0 && iso_refine(k, S.iso_scale, y, at) == 2;
+        if (!warm && !iso_local(k, S.iso_scale, y, at))
             break;
         int d[3];
         bool in = true, outer = false;
@@ -793,7 +795,7 @@ __device__ inline void make_support(const SceneDev &S, const double x[3], const 
         iso_cell(S, c, k);
         const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
         IsoAt at;
-        iso_local(k, y, at);
+        iso_local(k, S.iso_scale, y, at);
         iso_support<R>(k, c, at.r, sp);
     } else if constexpr (SH == 0) {
         for (int a = 0; a < 3; ++a) {
@@ -830,7 +832,7 @@ __device__ inline void iso_at(const SceneDev &S, const double x[3], const int c[
     IsoCell k;
     iso_cell(S, c, k);
     const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-    iso_local(k, y, at);
+    iso_local(k, S.iso_scale, y, at);
     iso_support<R>(k, c, at.r, sp);
 }
 

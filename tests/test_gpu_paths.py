@@ -526,3 +526,26 @@ def test_isoparametric_place_on_a_cell_axis_ends_at_rounding(mp):
             x += np.prod(np.where(o, r, 1 - r), axis=1)[:, None] * X[i[:, 2], i[:, 1], i[:, 0]]
         sc["x"] = x
         _check_nodal_mass(mp, sc, 1)
+
+
+@pytest.mark.parametrize("exponent", [-50, -42, 42, 50])
+def test_isoparametric_meshes_of_any_unit_of_length(mp, exponent):
+    """Cells of 1e-14 to 1e14: the scene scaled by a power of two, whose
+    results are those of the original, scaled."""
+    sc = _iso_body(122, 0.02)
+    L = 2.0 ** exponent
+    mesh, mat, sch = dict(sc["mesh"]), dict(sc["material"]), dict(sc["scheme"])
+    mesh.update(h=L * mesh["h"], node_x=L * np.asarray(mesh["node_x"]), origin=tuple(L * o for o in mesh["origin"]))
+    mat["rho"] = mat["rho"] / L ** 2
+    sch["gravity"] = tuple(L * g for g in sch["gravity"])
+    big = dict(sc, mesh=mesh, material=mat, scheme=sch, x=L * sc["x"], v=L * sc["v"], vol=L ** 3 * sc["vol"],
+               mass=L * sc["mass"])
+    ref = oracle.run(sc, 4)
+    c = mp.Context(0)
+    try:
+        s = c.create_scene(big, precision=mp.FP64)
+        s.step(4)
+        got = s.read()
+        check(f"iso-unit/{exponent}", {"x": got["x"] / L, "stress": got["stress"]}, ref, sc["x"], BARS["fp64"])
+    finally:
+        c.close()
