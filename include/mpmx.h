@@ -84,9 +84,13 @@ enum { MPMX_MEM_HOST = 0, MPMX_MEM_DEVICE = 1 };
 /* Scene error bits reported by mpmx_scene_stats (sticky: the scene stops at
  * the step that raised one).  OUT_OF_MESH and NONFINITE come from the
  * particles; TILE (a work item's particles spread beyond its LDS node tile)
- * and SORT (a reorder gave up waiting for one of its phases) are failures of
- * the implementation that its own rules exclude, reported rather than
- * silently mishandled; mpmx_scene_read maps them to MPMX_E_STATE. */
+ * and SORT (workgroups gave up waiting for others: for a phase of a reorder,
+ * after 1 s, or between the stages of a launch of many steps, after 10 s) are
+ * failures of the implementation that its own rules exclude, reported rather
+ * than silently mishandled; mpmx_scene_read maps them to MPMX_E_STATE.  After
+ * SORT from a reorder the particles are those of the last completed step;
+ * after SORT from a launch of many steps, which raises it on every scene of
+ * the batch, they and the step count are undefined. */
 enum {
     MPMX_ERRBIT_OUT_OF_MESH = 1u,
     MPMX_ERRBIT_NONFINITE = 2u,

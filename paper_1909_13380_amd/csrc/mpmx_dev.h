@@ -72,9 +72,11 @@ enum Ctl : int {
 
 // ERR_TILE: an item's particles spread beyond the LDS node tile, which the
 // reorder rule makes impossible; reported rather than silently mishandled.
-// ERR_SORT: the reorder kernel gave up waiting at a grid barrier (its
-// workgroups are all resident, so this does not happen); the particles stay
-// in their previous order.
+// ERR_SORT: the reorder kernel gave up waiting for a phase (whose chunks only
+// running workgroups hold, so this does not happen); the particles stay in
+// their previous order.  Or k_steps gave up waiting for its team or its next
+// list (the same): then every scene of the batch has it, particles may have
+// moved for part of a step, and the control words are not up to date.
 enum ErrBit : uint32_t { ERR_OUT_OF_MESH = 1u, ERR_NONFINITE = 2u, ERR_TILE = 4u, ERR_SORT = 8u };
 
 struct Item {

@@ -1339,12 +1339,12 @@ __device__ inline void store_rows(T *out, const T *lds, const uint32_t *pid, int
 
 // Particle state in original order (row-major doubles); any pointer of the
 // arrays may be null.  The scene's control words go to ctl (host memory), in
-// place of a copy of their own.  One workgroup takes kReadParticles consecutive particles (a full
-// brick's), loads their fields at once and stores them one by one through
-// LDS.  Storing each particle's words from its own lane left 8-byte pieces of
-// cache lines that two XCDs' L2s completed in part: 25.2M particles 3229 ->
-// 814 us, 2.1M 174 -> 71 us (staging all fields before one barrier holds 56
-// KB per workgroup and took 1560 and 113 us).
+// place of a copy of their own.  One workgroup takes kReadParticles consecutive
+// particles (a full brick's), loads their fields at once and stores them one
+// by one through LDS.  Storing each particle's words from its own lane left
+// 8-byte pieces of cache lines that two XCDs' L2s completed in part: 25.2M
+// particles 3229 -> 814 us, 2.1M 174 -> 71 us (staging all fields before one
+// barrier holds 56 KB per workgroup and took 1560 and 113 us).
 template <typename R>
 __global__ void __launch_bounds__(kReadThreads)
     k_read_out(const SceneDev *Sd, double *x, double *v, double *sig, double *vol, int32_t *cell, uint32_t *ctl)
