@@ -248,9 +248,9 @@ const char *mpmx_last_error(const mpmx_ctx *ctx);
  *                          per-kernel profiling is on, nor for USF batches
  *                          of at most about one work item (512 particles)
  *                          per compute unit on meshes of at most 2^18 bricks
- *                          (4x4x4 cells) in all, whose steps run in launches
- *                          of many steps each (unless this is 0 or
- *                          autotuning is off).
+ *                          (4x4x4 cells) in all, whose steps, in calls of
+ *                          more than a few, run in launches of many steps
+ *                          each (unless this is 0 or autotuning is off).
  *   MPMX_OPT_AUTOTUNE      1 (default): on the first call that runs at least
  *                          MPMX_TUNE_MIN_STEPS steps on a batch layout
  *                          (precision, shape function, algorithm and the

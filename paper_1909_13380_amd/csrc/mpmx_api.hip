@@ -731,9 +731,13 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 // 62.5, 94, 73.  The wide shape at 2, 3, 4 and 6 per compute unit: 44.3, 40.6,
 // 41.5, 42.1 (10648 particles).
 //
-// Calls of fewer than three steps have nothing to share; profiled,
-// always-sorting and fixed-shape (no autotuning or graphs) calls keep one
-// launch per kernel.
+// A launch costs about 25 us beyond its steps (its workgroups start, meet and
+// end), so a call needs some of them.  Whole calls of n steps in separate
+// kernels and in k_steps, 32768 particles (us): linear n = 3: 98, 121; n = 5:
+// 152, 156; n = 6: 177, 173; n = 8: 226, 205 (FP64 n = 5: 153, 164; n = 6: 183,
+// 183; 256 scenes of one cell n = 5: 183, 191; n = 6: 202, 203); GIMP n = 3:
+// 188, 162; isoparametric n = 3: 153, 148.  Profiled, always-sorting and
+// fixed-shape (no autotuning or graphs) calls keep one launch per kernel.
 //
 // A reorder inside the launch reads every brick's counters with half the
 // wavefronts of the reorder kernel.  Per reorder (4096 particles, us), in its
@@ -744,10 +748,11 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 // one launch per kernel.
 constexpr int64_t kStepsPerLaunch = 1024, kWideStepsPerLaunch = 128, kStepsBricks = 1 << 18;
 constexpr int kWidePerCu = 3;
+constexpr int64_t kStepsLeast[3] = {5, 2, 2};   // by kernel shape: linear, GIMP, isoparametric
 
-bool steps_at_once(const mpmx_ctx *ctx, const Batch &b)
+bool steps_at_once(const mpmx_ctx *ctx, const Batch &b, int64_t left)
 {
-    return ctx->autotune && ctx->graph_steps > 0 && !ctx->prof.on && b.algo == MPMX_USF && !b.always &&
+    return left >= kStepsLeast[b.shape] && ctx->autotune && ctx->graph_steps > 0 && !ctx->prof.on && b.algo == MPMX_USF && !b.always &&
            b.items <= ctx->num_cu && b.bd.total_bricks <= kStepsBricks;
 }
 
@@ -1010,7 +1015,7 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
     }
     ctx->last = cfg;
     const int K = ctx->graph_steps;
-    if (left >= 2 && steps_at_once(ctx, b)) {
+    if (steps_at_once(ctx, b, left)) {
         if ((rc = enqueue_steps(ctx, b, left)))
             return rc;
         return mark_queued(ctx, b);

@@ -549,3 +549,29 @@ def test_isoparametric_meshes_of_any_unit_of_length(mp, exponent):
         check(f"iso-unit/{exponent}", {"x": got["x"] / L, "stress": got["stress"]}, ref, sc["x"], BARS["fp64"])
     finally:
         c.close()
+
+
+def test_calls_of_few_steps_cost_no_more_than_in_separate_kernels(mp):
+    """Calls of three steps of a small linear body, against the separate
+    kernels: as much (1.24 times their time in a launch of their own, which
+    costs more than two steps save)."""
+    import time
+    import torch
+    sc = scenes.random_block(n_cells=(16, 16, 16), mesh_cells=(36, 36, 36), seed=7, vel=0.01, dt=1e-5,
+                             gravity=(0.0, 0.0, 0.0), bc=scenes.walls(floor=scenes.FREE, sides=scenes.FREE))
+    c = [mp.Context(0), mp.Context(0)]
+    c[1].set_option(mp.OPT_AUTOTUNE, 0)
+    ss = [x.create_scene(sc, precision=mp.FP32) for x in c]
+    t = [[], []]
+    for k in range(300):
+        for i in (0, 1):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            ss[i].step(3)
+            torch.cuda.synchronize()
+            t[i].append(time.perf_counter() - t0)
+    t = [float(np.median(a)) for a in t]
+    print(f"[few-steps] {t[0] * 1e6:.1f} us, separate kernels {t[1] * 1e6:.1f} us", flush=True)
+    for x in c:
+        x.close()
+    assert t[0] < 1.15 * t[1], t
