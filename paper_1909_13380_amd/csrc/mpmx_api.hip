@@ -80,6 +80,7 @@ struct Batch {
     int prec = 0, shape = 0, algo = 0;
     bool always = false;    // some scene reorders after every step
     int64_t items = 0;      // sum of the items of the scenes that the present call steps
+    int64_t room = 0;       // sum of their rooms
     // the last queued steps of this batch (its image is free to rewrite
     // once they are done)
     std::shared_ptr<StepEvent> last_use;
@@ -174,6 +175,7 @@ struct Scene {
     bool main_sync = false;
     bool fresh = true;       // no steps queued yet: its first step reorders
     int64_t items = 0;       // work items: of the particles as loaded (estimate), later as last reported
+    int64_t room = 0;        // items to leave room for: some more than that
 };
 
 }  // namespace
@@ -720,14 +722,14 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 // Beyond one item per workgroup the separate kernels win, with several
 // smaller workgroups resident on each compute unit.  The host knows the items
 // as last reported to it (until then, the bricks of the extent as loaded).  A
-// body that spreads over more of them within a call leaves the launch, and
-// the call's remaining steps run in launches of the wide shape (128 threads,
-// kWidePerCu workgroups per compute unit), which are queued behind it and
-// return at once (2 us) where it was not left.  Per step, over the whole call,
-// in separate kernels, with the one shape only, and with both (us): 85184
-// particles that spread from 216 to 729 items 30.0, 39.5, 29.3, to 2744 items
-// 46.0, 69.8, 49.0; 10648 particles to 2924 items 38.0, 57.7, 40.6 (GIMP 58.8,
-// 86.9, 55.3); 12167 particles to 3114 items with a reorder every other step
+// body that spreads over more of them than the launch has workgroups leaves
+// it, and the call's remaining steps run in launches of the wide shape (128
+// threads, kWidePerCu workgroups per compute unit), which are queued behind it
+// and return at once (2 us) where it was not left.  Per step, over the whole
+// call, in separate kernels, with the one shape only, and with both (us):
+// 85184 particles that spread from 216 to 729 items 30.0, 39.5, 29.3, to 2744
+// items 46.0, 69.8, 49.0; 10648 particles to 2924 items 38.0, 57.7, 40.6 (GIMP
+// 58.8, 86.9, 55.3); 12167 particles to 3114 items with a reorder every other step
 // 62.5, 94, 73.  The wide shape at 2, 3, 4 and 6 per compute unit: 44.3, 40.6,
 // 41.5, 42.1 (10648 particles).
 //
@@ -746,7 +748,7 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 // moves 0.1 cells a step, 274625 bricks 36.1, 34.8 (0.3 cells 55.4, 57.7);
 // 1081665 bricks 47.0, 54.7.  So meshes of more than kStepsBricks bricks keep
 // one launch per kernel.
-constexpr int64_t kStepsPerLaunch = 1024, kWideStepsPerLaunch = 128, kStepsBricks = 1 << 18;
+constexpr int64_t kStepsPerLaunch = 1024, kWideStepsPerLaunch = 128, kStepsBricks = 1 << 18, kTeamBricks = 512;
 constexpr int kWidePerCu = 3;
 constexpr int64_t kStepsLeast[3] = {5, 2, 2};   // by kernel shape: linear, GIMP, isoparametric
 
@@ -760,9 +762,8 @@ int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)
 {
     const KernelSet &K = kernel_set(b.prec, b.shape);
     BatchDev bd = b.bd;
-    const uint32_t cus = (uint32_t)ctx->num_cu;
-    auto queue = [&](const void *fn, int threads, int per_cu, int64_t per_launch, uint32_t limit) {
-        const dim3 grid((unsigned)std::clamp<int64_t>(bd.max_items, 1, (int64_t)per_cu * cus));
+    auto queue = [&](const void *fn, int threads, int64_t most, int64_t per_launch, uint32_t limit) {
+        const dim3 grid((unsigned)std::clamp<int64_t>(bd.max_items, 1, most));
         for (int64_t todo = left; todo > 0;) {
             uint32_t n = (uint32_t)std::min(todo, per_launch);
             void *args[] = {&bd, &n, &limit};
@@ -772,9 +773,15 @@ int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)
         }
         return (int)MPMX_OK;
     };
-    if (int rc = queue(K.steps, kStepThreads, 1, kStepsPerLaunch, cus))
+    // one workgroup per item that the call may come to, or per kTeamBricks
+    // bricks of its reorders; no more, so that other contexts' launches find
+    // compute units free: two contexts with 32768 particles each, 100 steps
+    // and a read at once (us): separate kernels 2761, a workgroup on every
+    // compute unit 3345, this 1977
+    const int64_t team = std::clamp<int64_t>(std::max(b.room, ceil_div(bd.total_bricks, kTeamBricks)), 1, ctx->num_cu);
+    if (int rc = queue(K.steps, kStepThreads, team, kStepsPerLaunch, (uint32_t)team))
         return rc;
-    if (bd.max_items <= cus)   // never more items than that
+    if (bd.max_items <= team)   // never more items than that
         return MPMX_OK;
     int &per_cu = ctx->wide_per_cu[b.prec ? 1 : 0][b.shape];
     if (per_cu == 0) {
@@ -784,7 +791,7 @@ int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)
             occ = 1;
         per_cu = std::min(occ, kWidePerCu);
     }
-    return queue(K.steps_wide, kStepWideThreads, per_cu, kWideStepsPerLaunch, 0u);
+    return queue(K.steps_wide, kStepWideThreads, (int64_t)per_cu * ctx->num_cu, kWideStepsPerLaunch, 0u);
 }
 
 uint64_t layout_key(const Batch &b)
@@ -995,7 +1002,7 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
         }
     }
     bool fresh = false;
-    b.items = 0;
+    b.items = b.room = 0;
     for (int i = 0; i < n; ++i) {
         Scene *s = ns[i] > 0 ? find(ctx, b.ids[i]) : nullptr;
         if (!s)
@@ -1003,6 +1010,7 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
         fresh = fresh || s->fresh;
         s->fresh = false;
         b.items += s->items;
+        b.room += s->room;
     }
     if ((rc = enqueue_step(ctx, b, cfg, true, fresh || b.always, nullptr)))
         return rc;
@@ -1042,8 +1050,10 @@ int run_steps(mpmx_ctx *ctx, Batch &b, const int64_t *nsteps, int64_t uniform)
 // that has not been reordered yet has none).
 void note_items(Scene *s, const uint32_t *ctl)
 {
-    if (ctl[CTL_N_SORTS] > 0)
+    if (ctl[CTL_N_SORTS] > 0) {
         s->items = ctl[CTL_N_ITEMS];
+        s->room = s->items + s->items / 4 + 1;
+    }
 }
 
 int read_ctl(mpmx_ctx *ctx, Scene *s, uint32_t *ctl)
@@ -1582,11 +1592,16 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
                     ctl[CTL_ERR]);
     }
     // items of the loaded particles, if they fill the bricks of their extent
+    // (once they move, up to one brick more per axis)
     if (np > 0) {
-        int64_t bricks = 1;
-        for (int a = 0; a < 3; ++a)
-            bricks *= ceil_div((int64_t)ctl[CTL_TOP + a] - (int64_t)ctl[CTL_LOW + a] + 1, kBrick);
+        int64_t bricks = 1, moved = 1;
+        for (int a = 0; a < 3; ++a) {
+            const int64_t n = ceil_div((int64_t)ctl[CTL_TOP + a] - (int64_t)ctl[CTL_LOW + a] + 1, kBrick);
+            bricks *= n;
+            moved *= n + 1;
+        }
         s->items = std::max(std::min(bricks, np), ceil_div(np, kChunk));
+        s->room = std::max(std::min(moved, np), ceil_div(np, kChunk)) + 1;
     }
     std::vector<Scene *> one{s};
     rc = build_batch(ctx, s->single, one);
