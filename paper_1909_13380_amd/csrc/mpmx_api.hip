@@ -1819,7 +1819,8 @@ int mpmx_scene_read(mpmx_ctx *ctx, uint64_t scene, const mpmx_particles_out *out
         SceneDev *d = s->d;
         void *args[] = {&d, &dst[0], &dst[1], &dst[2], &dst[3], &dst[4], &ctl};
         const dim3 rg((unsigned)std::min<int64_t>(ceil_div(np, kReadParticles), 1 << 20));
-        if (hipLaunchKernel(K.read_out, rg, dim3(kReadThreads), args, 0, ctx->aux) != hipSuccess)
+        const bool all = std::all_of(host, host + 5, [](const void *q) { return q != nullptr; });
+        if (hipLaunchKernel(all ? K.read_all : K.read_out, rg, dim3(kReadThreads), args, 0, ctx->aux) != hipSuccess)
             ok = false;
         if (ok && to_host && total && small &&
             hipMemcpyAsync(ctx->pinned + kPinnedArrays, stage, total, hipMemcpyDeviceToHost, ctx->aux) != hipSuccess)

@@ -1340,12 +1340,13 @@ __device__ inline void store_rows(T *out, const T *lds, const uint32_t *pid, int
 // Particle state in original order (row-major doubles); any pointer of the
 // arrays may be null.  The scene's control words go to ctl (host memory), in
 // place of a copy of their own.  One workgroup takes kReadParticles consecutive
-// particles (a full brick's), loads their fields at once and stores them one
-// by one through LDS.  Storing each particle's words from its own lane left
+// particles (a full brick's), loads the fields asked for at once (ALL: every
+// one, with no branch between the loads) and stores them one by one through
+// LDS.  Storing each particle's words from its own lane left
 // 8-byte pieces of cache lines that two XCDs' L2s completed in part: 25.2M
 // particles 3229 -> 814 us, 2.1M 174 -> 71 us (staging all fields before one
 // barrier holds 56 KB per workgroup and took 1560 and 113 us).
-template <typename R>
+template <typename R, bool ALL>
 __global__ void __launch_bounds__(kReadThreads)
     k_read_out(const SceneDev *Sd, double *x, double *v, double *sig, double *vol, int32_t *cell, uint32_t *ctl)
 {
@@ -1372,14 +1373,19 @@ __global__ void __launch_bounds__(kReadThreads)
                 continue;
             const int64_t p = p0 + q;
             pid[q] = S.pid[cur][p];
-            for (int a = 0; a < 3; ++a) {
-                px[u][a] = X[a * n + p];
-                pv[u][a] = V[a * n + p];
-            }
-            for (int k = 0; k < 6; ++k)
-                ps[u][k] = SG[k * n + p];
-            pvo[u] = VO[p];
-            pc[u] = S.cell[cur][p];
+            if (ALL || x)
+                for (int a = 0; a < 3; ++a)
+                    px[u][a] = X[a * n + p];
+            if (ALL || v)
+                for (int a = 0; a < 3; ++a)
+                    pv[u][a] = V[a * n + p];
+            if (ALL || sig)
+                for (int k = 0; k < 6; ++k)
+                    ps[u][k] = SG[k * n + p];
+            if (ALL || vol)
+                pvo[u] = VO[p];
+            if (ALL || cell)
+                pc[u] = S.cell[cur][p];
         }
         // stage one field with put(u, row slot), then store its rows
         auto field = [&](auto put, auto store) {
@@ -4756,7 +4762,8 @@ static KernelSet make_set()
 {
     KernelSet k;
     k.load = (const void *)&k_load<R>;
-    k.read_out = (const void *)&k_read_out<R>;
+    k.read_out = (const void *)&k_read_out<R, false>;
+    k.read_all = (const void *)&k_read_out<R, true>;
     k.nodes_out = (const void *)&k_nodes_out<R>;
     k.reorder = (const void *)&k_reorder<R>;
     k.sort_move = (const void *)&k_sort_move<R>;

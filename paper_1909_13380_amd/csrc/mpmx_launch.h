@@ -13,7 +13,8 @@ constexpr int kNumItemThreadChoices = 3;
 // also per workgroup size (index into kItemThreadChoices).
 struct KernelSet {
     const void *load;       // (SceneDev*, x, v, sig, vol, mass)
-    const void *read_out;   // (const SceneDev*, x, v, sig, vol, cell, ctl)
+    const void *read_out;   // (const SceneDev*, x, v, sig, vol, cell, ctl), any of the arrays null
+    const void *read_all;   // the same, none of them null
     const void *nodes_out;  // (const SceneDev*, m, p, f)
     const void *reorder;    // (BatchDev): reorder, then the step control
     const void *steps;      // (BatchDev, steps, items): many USF steps in one launch (small batches)
