@@ -1447,8 +1447,8 @@ int mpmx_scene_create(mpmx_ctx *ctx, const mpmx_mesh *mesh, const mpmx_material 
             edge = std::max(edge, *ends.second - *ends.first);
         }
         edge /= (double)std::max({mesh->n[0], mesh->n[1], mesh->n[2]});
-        const bool fine = edge > 0.0 && std::isfinite(edge);
-        h.iso_scale = fine ? std::ldexp(1.0f, std::clamp(-std::ilogb(edge), -120, 120)) : 1.0f;
+        const bool fine = !(edge > 0.0) || !std::isfinite(edge) || (edge > 1e-9 && edge < 1e9);
+        h.iso_scale = fine ? 1.0f : std::ldexp(1.0f, std::clamp(-std::ilogb(edge), -120, 120));
     }
     // uploads go through the second stream, so that they overlap steps
     // already queued on the context stream

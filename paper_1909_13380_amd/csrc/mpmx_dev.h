@@ -99,7 +99,7 @@ struct SceneDev {
     double origin[3];
     double h, inv_h;
     const double *X;   // isoparametric mesh: node positions x[3][nn] (FP64); null for the uniform grid
-    float iso_scale;   // isoparametric mesh: about one over the cells' edge, a power of two
+    float iso_scale;   // isoparametric mesh: unit of the location's step matrix (1, or a power of two)
     int n[3];        // cells
     int nb[3];       // bricks per axis: room for every brick shift
     int cmin[3];     // smallest cell of the particles at creation (sets the brick shift)

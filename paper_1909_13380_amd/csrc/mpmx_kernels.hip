@@ -507,17 +507,20 @@ __device__ inline void iso_point(const IsoCell &k, const double r[3], double x[3
 }
 
 // A place in an isoparametric cell: local coordinates r, and the step matrix
-// Mi that located them: (dx/dr)^-1 in FP32 at a point within `off` (maximum
+// Mi that located them: (dx/dr)^-1 in FP32 at a point within kIsoNear (maximum
 // norm) of r.
 struct IsoAt {
     double r[3];
     float Mi[3][3];
-    float off;
 };
 
+constexpr float kIsoNear = 3e-6f;
+constexpr float kIsoRound = 1e-6f;   // what the matrix's rounding leaves of a step
+
 // The step matrix at the place itself.  The scale s (SceneDev::iso_scale, a
-// power of two, so exact) is about one over the cells' edge: without it the
-// determinant leaves the range of FP32 for edges below 1e-13 or above 1e12.
+// power of two, so exact) is about one over the cells' edge where that is
+// below 1e-9 or above 1e9, else 1: the determinant would leave the range of
+// FP32 for edges below 1e-13 or above 1e12.
 __device__ inline void iso_step_matrix(const IsoCell &k, float s, IsoAt &at)
 {
     const float r[3] = {(float)at.r[0], (float)at.r[1], (float)at.r[2]};
@@ -528,14 +531,18 @@ __device__ inline void iso_step_matrix(const IsoCell &k, float s, IsoAt &at)
         float b[7];
         for (int q = 0; q < 7; ++q)
             b[q] = (float)k.b[q][a];
-        M[a][0] = s * (b[0] + b[3] * r[1] + b[5] * r[2] + b[6] * st);
-        M[a][1] = s * (b[1] + b[3] * r[0] + b[4] * r[2] + b[6] * rt);
-        M[a][2] = s * (b[2] + b[4] * r[1] + b[5] * r[0] + b[6] * rs);
+        M[a][0] = b[0] + b[3] * r[1] + b[5] * r[2] + b[6] * st;
+        M[a][1] = b[1] + b[3] * r[0] + b[4] * r[2] + b[6] * rt;
+        M[a][2] = b[2] + b[4] * r[1] + b[5] * r[0] + b[6] * rs;
     }
+    if (s != 1.0f)   // (the same for every lane)
+        for (int a = 0; a < 3; ++a)
+            for (int c = 0; c < 3; ++c)
+                M[a][c] *= s;
     const float c00 = M[1][1] * M[2][2] - M[1][2] * M[2][1];
     const float c01 = M[1][2] * M[2][0] - M[1][0] * M[2][2];
     const float c02 = M[1][0] * M[2][1] - M[1][1] * M[2][0];
-    const float id = s * (1.0f / (M[0][0] * c00 + M[0][1] * c01 + M[0][2] * c02));
+    const float id = s / (M[0][0] * c00 + M[0][1] * c01 + M[0][2] * c02);
     Mi[0][0] = c00 * id;
     Mi[1][0] = c01 * id;
     Mi[2][0] = c02 * id;
@@ -549,6 +556,18 @@ __device__ inline void iso_step_matrix(const IsoCell &k, float s, IsoAt &at)
 
 // One step of the location of the point o + y: at.r -= Mi (x(r) - y).
 // Returns the step's size.
+//
+// The residual x(r) - y is FP64, the step FP32: what the step matrix lacks in
+// accuracy only scales the error that a step leaves, to about the distance of
+// the point that it belongs to (times the cell's bend) plus kIsoRound, in parts
+// of the step.  The iterations below end where that is FP64 rounding.
+// Stopping at a step of 1e-10 and evaluating the matrix only after steps above
+// 1e-5 left up to 9e-13 after a move of 0.01 of a cell, and 6e-11 where the
+// point lies on an axis through the cell's centre, along which the residual
+// vanishes but the matrix changes (unit cells whose nodes are off by up to
+// 0.3).  A step costs 21 + 9 operations where Newton-Raphson in FP64
+// throughout cost about 110 (1.05M particles: g2p_p2g 76.3 -> 59.7 us, stress
+// 48.0 -> 42.7; with the looser end 59.0 and 42.7).
 __device__ inline float iso_step(const IsoCell &k, const double y[3], IsoAt &at)
 {
     double x[3];
@@ -560,51 +579,59 @@ __device__ inline float iso_step(const IsoCell &k, const double y[3], IsoAt &at)
         at.r[a] -= (double)d;
         dmax = fmaxf(dmax, fabsf(d));
     }
-    at.off += dmax;
     return dmax;
 }
 
-// Refine the place of the point o + y.  The residual x(r) - y is FP64, the
-// step FP32: what the step matrix lacks in accuracy only scales the error that
-// a step leaves, to about `off` (it belongs to a point at that distance) plus
-// 1e-6 (its rounding) of the step.  The iteration ends where that is at most
-// 2e-16, FP64 rounding, and evaluates the matrix again (Newton-Raphson, the
-// price of one to two steps) where the next two steps would not end it.
-// Evaluated against extended precision over unit cells whose nodes are off by
-// up to 0.3: at most 1.3e-15 after moves of 0 to 0.05 of a cell, warm or cold
-// (stopping at a step of 1e-10 and evaluating the matrix only after steps
-// above 1e-5 left up to 9e-13 after a move of 0.01, and 6e-11 where the point
-// lies on an axis through the cell's centre, along which the residual vanishes
-// but the matrix changes).  A step costs 21 + 9 operations where
-// Newton-Raphson in FP64 throughout cost about 110 (1.05M particles: g2p_p2g
-// 76.3 -> 60.7 us, stress 48.0 -> 43.3; with the looser end 59.1 and 42.7).
-// 2: converged; 1: not within 50 steps; 0: broke down.
-__device__ inline int iso_refine(const IsoCell &k, float s, const double y[3], IsoAt &at)
+__device__ inline bool iso_finite(const IsoAt &at)
 {
-    int done = 1;
-    for (int it = 0; it < 50; ++it) {
-        const float d = iso_step(k, y, at);
-        if (!(d > 1e-10f) && !(d * at.off > 2e-16f)) {   // converged, or not a number (the check below fails)
-            done = 2;
-            break;
-        }
-        if (d * at.off * at.off * at.off > 1e-15f) {
-            iso_step_matrix(k, s, at);
-            at.off = 0.0f;
-        }
-    }
-    return isfinite(at.r[0]) && isfinite(at.r[1]) && isfinite(at.r[2]) ? done : 0;
+    return isfinite(at.r[0]) && isfinite(at.r[1]) && isfinite(at.r[2]);
 }
 
-// The same from the affine guess r0 = 1/2 + J(1/2)^-1 (y - x(1/2)), the
-// refinement's first step from the centre.  False if it broke down.
+// The place of the point o + y from the affine guess r0 = 1/2 + J(1/2)^-1 (y -
+// x(1/2)), the first step from the centre.  The matrix is evaluated again
+// after the next step, however small (see above), and after every one beyond
+// kIsoNear, so that it belongs to a point at most that far when a step of
+// 1e-10 ends the iteration.  False if it broke down.
 __device__ inline bool iso_local(const IsoCell &k, float s, const double y[3], IsoAt &at)
 {
     at.r[0] = at.r[1] = at.r[2] = 0.5;
     iso_step_matrix(k, s, at);
-    at.off = 0.0f;
     (void)iso_step(k, y, at);
-    return iso_refine(k, s, y, at) != 0;
+    for (int it = 0; it < 50; ++it) {
+        const float d = iso_step(k, y, at);
+        if (!(d > (it ? 1e-10f : 1e-15f)))   // converged, or not a number (the check below fails)
+            break;
+        if (it == 0 || d > kIsoNear)
+            iso_step_matrix(k, s, at);
+    }
+    return iso_finite(at);
+}
+
+// The place of the point o + y from a guess with a step matrix of a point at a
+// distance of up to `off`.  bend bounds what of J changes with r, relative to
+// J, so a step leaves at most bend off + kIsoRound of itself.  The matrix is
+// evaluated again (the price of one to two steps) where the next two steps
+// would not end the iteration.  False if it broke down or did not converge.
+__device__ inline bool iso_refine(const IsoCell &k, float s, const double y[3], IsoAt &at, float off)
+{
+    float bend = 0.0f, inv = 0.0f;
+    for (int a = 0; a < 3; ++a) {
+        bend = fmaxf(bend, (float)(fabs(k.b[3][a]) + fabs(k.b[4][a]) + fabs(k.b[5][a]) + 3.0 * fabs(k.b[6][a])));
+        inv = fmaxf(inv, fabsf(at.Mi[a][0]) + fabsf(at.Mi[a][1]) + fabsf(at.Mi[a][2]));
+    }
+    bend *= 2.0f * inv;
+    for (int it = 0; it < 50; ++it) {
+        const float d = iso_step(k, y, at);
+        off += d;
+        const float leaves = bend * off + kIsoRound, left = d * leaves;
+        if (!(left > 2e-16f))   // converged, or not a number
+            return iso_finite(at);
+        if (left * leaves * leaves > 2e-16f) {
+            iso_step_matrix(k, s, at);
+            off = 0.0f;
+        }
+    }
+    return false;
 }
 
 // Cell of point x on an isoparametric mesh by a walk across cell faces from
@@ -619,7 +646,7 @@ __device__ inline bool iso_local(const IsoCell &k, float s, const double y[3], I
 // or ERR_OUT_OF_MESH / ERR_NONFINITE.
 template <bool WARM>
 __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int c[3], IsoCell &k, IsoAt &at,
-                                      int budget)
+                                      int budget, float off = 0.0f)
 {
     double(&r)[3] = at.r;
     if (!isfinite(x[0]) || !isfinite(x[1]) || !isfinite(x[2]))
@@ -629,7 +656,7 @@ __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int 
     for (int m = 0; m < budget; ++m) {
         iso_cell(S, c, k);
         const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-        const bool warm = WARM && m == 0 && iso_refine(k, S.iso_scale, y, at) == 2;
+        const bool warm = WARM && m == 0 && iso_refine(k, S.iso_scale, y, at, off);
         if (!warm && !iso_local(k, S.iso_scale, y, at))
             break;
         int d[3];
@@ -846,9 +873,8 @@ __device__ inline uint32_t iso_moved(const SceneDev &S, const double x[3], const
         at.r[a] += (double)d;
         far = fmaxf(far, fabsf(d));
     }
-    at.off += far;
     IsoCell k;
-    return iso_locate<true>(S, x, nc, k, at, kIsoWalk);
+    return iso_locate<true>(S, x, nc, k, at, kIsoWalk, far + kIsoNear);
 }
 
 // --------------------------------------------------------- constitutive --
