@@ -754,8 +754,8 @@ constexpr int64_t kStepsLeast[3] = {5, 2, 2};   // by kernel shape: linear, GIMP
 
 bool steps_at_once(const mpmx_ctx *ctx, const Batch &b, int64_t left)
 {
-    return left >= kStepsLeast[b.shape] && ctx->autotune && ctx->graph_steps > 0 && !ctx->prof.on && b.algo == MPMX_USF && !b.always &&
-           b.items <= ctx->num_cu && b.bd.total_bricks <= kStepsBricks;
+    return b.algo == MPMX_USF && !b.always && left >= kStepsLeast[b.shape] && b.items <= ctx->num_cu &&
+           b.bd.total_bricks <= kStepsBricks && ctx->autotune && ctx->graph_steps > 0 && !ctx->prof.on;
 }
 
 int enqueue_steps(mpmx_ctx *ctx, Batch &b, int64_t left)

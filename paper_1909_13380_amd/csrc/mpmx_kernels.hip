@@ -1246,8 +1246,8 @@ __device__ inline void clear_remap_previous(const BatchDev &B)
 // Inputs are row-major doubles (n x 3, n x 6, n); fills particle buffer 0,
 // sets the identity permutation and each particle's cell.
 template <typename R>
-__global__ void __launch_bounds__(kLoadThreads) k_load(SceneDev *Sd, const double *x, const double *v, const double *sig, const double *vol,
-                       const double *mass)
+__global__ void __launch_bounds__(kLoadThreads)
+    k_load(SceneDev *Sd, const double *x, const double *v, const double *sig, const double *vol, const double *mass)
 {
     const SceneDev &S = *Sd;
     const int64_t n = S.np;
@@ -1311,9 +1311,9 @@ __global__ void __launch_bounds__(kLoadThreads) k_load(SceneDev *Sd, const doubl
             }
     }
     // the smallest cell per axis (sets the brick shift) and the largest: one
-    // atomic per workgroup, and only where it changes the value read before it.  One per
-    // wavefront and axis, all on one cache line, set this kernel's time
-    // (1950 us for 2.1M particles).
+    // atomic per workgroup, and only where it changes the value read before
+    // it.  One per wavefront and axis, all on one cache line, set this kernel's
+    // time (1950 us for 2.1M particles).
     __shared__ int ext[6][kLoadThreads / 64];
     for (int a = 0; a < 3; ++a) {
         const int lo = wave_reduce<false>(mn[a]), hi = wave_reduce<true>(mx[a]);
@@ -3600,9 +3600,9 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 }
 
 // ------------------------------------------------ many steps, one launch --
-// k_steps runs the remaining steps of a small USF batch in one launch: one
-// workgroup per compute unit, each keeping its items (and their particles)
-// from step to step.  The two stages of a step are separated by a grid
+// k_steps runs the remaining steps of a small USF batch in one launch: a
+// workgroup per item (the host's guess of how many it takes), each keeping its
+// items and their particles from step to step.  The two stages of a step are separated by a grid
 // barrier in place of the kernel boundaries, and the step control and the
 // items' start are paid once.  Between workgroups only the node buffers are
 // shared: they are written with agent-scope atomics (adds, and the zeroing)
@@ -3635,7 +3635,8 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 //
 // A step is bound by the chain of latencies of one item's two stages (about
 // 5 us each) and two barriers.  512 threads, one particle each, keep that
-// chain shortest (no loop over particles).  Measured per step against the
+// chain shortest (no loop over particles); with more items than workgroups the
+// shape of 128 threads and several workgroups per compute unit wins.  Measured per step against the
 // separate kernels: 1000 particles 18.9 -> 14.6 us (GIMP 29.1 -> 20.5, FP64
 // 18.9 -> 16.7, isoparametric 25.1 -> 20.0), 51200 particles 22.0 -> 16.8 us.
 
