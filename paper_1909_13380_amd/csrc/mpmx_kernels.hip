@@ -507,14 +507,15 @@ __device__ inline void iso_point(const IsoCell &k, const double r[3], double x[3
 }
 
 // A place in an isoparametric cell: local coordinates r, and the step matrix
-// Mi that located them: (dx/dr)^-1 in FP32 at a point within kIsoNear (maximum
+// Mi that located them: (dx/dr)^-1 in FP32 at a point within `off` (maximum
 // norm) of r.
 struct IsoAt {
     double r[3];
     float Mi[3][3];
+    float off;
+    float bend;   // the cell's, see iso_bend()
 };
 
-constexpr float kIsoNear = 3e-6f;
 constexpr float kIsoRound = 1e-6f;   // what the matrix's rounding leaves of a step
 
 // The step matrix at the place itself.  The scale s (SceneDev::iso_scale, a
@@ -587,51 +588,53 @@ __device__ inline bool iso_finite(const IsoAt &at)
     return isfinite(at.r[0]) && isfinite(at.r[1]) && isfinite(at.r[2]);
 }
 
-// The place of the point o + y from the affine guess r0 = 1/2 + J(1/2)^-1 (y -
-// x(1/2)), the first step from the centre.  The matrix is evaluated again
-// after the next step, however small (see above), and after every one beyond
-// kIsoNear, so that it belongs to a point at most that far when a step of
-// 1e-10 ends the iteration.  False if it broke down.
-__device__ inline bool iso_local(const IsoCell &k, float s, const double y[3], IsoAt &at)
+// Twice the largest sum |b4| + |b5| + |b6| + 3 |b7| of a component: a bound of
+// how much a row of dx/dr changes with r in [0, 1]^3.
+__device__ inline float iso_bend(const IsoCell &k)
 {
-    at.r[0] = at.r[1] = at.r[2] = 0.5;
-    iso_step_matrix(k, s, at);
-    (void)iso_step(k, y, at);
-    for (int it = 0; it < 50; ++it) {
-        const float d = iso_step(k, y, at);
-        if (!(d > (it ? 1e-10f : 1e-15f)))   // converged, or not a number (the check below fails)
-            break;
-        if (it == 0 || d > kIsoNear)
-            iso_step_matrix(k, s, at);
-    }
-    return iso_finite(at);
+    float m = 0.0f;
+    for (int a = 0; a < 3; ++a)
+        m = fmaxf(m, fabsf((float)k.b[3][a]) + fabsf((float)k.b[4][a]) + fabsf((float)k.b[5][a]) +
+                         3.0f * fabsf((float)k.b[6][a]));
+    return 2.0f * m;
 }
 
-// The place of the point o + y from a guess with a step matrix of a point at a
-// distance of up to `off`.  bend bounds what of J changes with r, relative to
-// J, so a step leaves at most bend off + kIsoRound of itself.  The matrix is
-// evaluated again (the price of one to two steps) where the next two steps
-// would not end the iteration.  False if it broke down or did not converge.
-__device__ inline bool iso_refine(const IsoCell &k, float s, const double y[3], IsoAt &at, float off)
+// The place of the point o + y from a guess and a step matrix: a step leaves at most bend (relative to dx/dr) off +
+// kIsoRound of itself.  The matrix is evaluated again (the price of one to two
+// steps) where the next two steps would not end the iteration.  False if it
+// broke down or did not converge.
+__device__ inline bool iso_refine(const IsoCell &k, float s, const double y[3], IsoAt &at)
 {
-    float bend = 0.0f, inv = 0.0f;
-    for (int a = 0; a < 3; ++a) {
-        bend = fmaxf(bend, (float)(fabs(k.b[3][a]) + fabs(k.b[4][a]) + fabs(k.b[5][a]) + 3.0 * fabs(k.b[6][a])));
+    float inv = 0.0f;
+    for (int a = 0; a < 3; ++a)
         inv = fmaxf(inv, fabsf(at.Mi[a][0]) + fabsf(at.Mi[a][1]) + fabsf(at.Mi[a][2]));
-    }
-    bend *= 2.0f * inv;
+    const float bend = at.bend * inv;
     for (int it = 0; it < 50; ++it) {
         const float d = iso_step(k, y, at);
-        off += d;
-        const float leaves = bend * off + kIsoRound, left = d * leaves;
+        at.off += d;
+        const float leaves = bend * at.off + kIsoRound, left = d * leaves;
         if (!(left > 2e-16f))   // converged, or not a number
             return iso_finite(at);
         if (left * leaves * leaves > 2e-16f) {
             iso_step_matrix(k, s, at);
-            off = 0.0f;
+            at.off = 0.0f;
         }
     }
     return false;
+}
+
+// The same from the affine guess r0 = 1/2 + J(1/2)^-1 (y - x(1/2)), the first
+// step from the centre, with the matrix at the guess.  False if it broke down.
+__device__ inline bool iso_local(const IsoCell &k, float s, const double y[3], IsoAt &at)
+{
+    at.bend = iso_bend(k);
+    at.r[0] = at.r[1] = at.r[2] = 0.5;
+    iso_step_matrix(k, s, at);
+    (void)iso_step(k, y, at);
+    iso_step_matrix(k, s, at);
+    at.off = 0.0f;
+    (void)iso_refine(k, s, y, at);
+    return iso_finite(at);
 }
 
 // Cell of point x on an isoparametric mesh by a walk across cell faces from
@@ -646,7 +649,7 @@ __device__ inline bool iso_refine(const IsoCell &k, float s, const double y[3], 
 // or ERR_OUT_OF_MESH / ERR_NONFINITE.
 template <bool WARM>
 __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int c[3], IsoCell &k, IsoAt &at,
-                                      int budget, float off = 0.0f)
+                                      int budget)
 {
     double(&r)[3] = at.r;
     if (!isfinite(x[0]) || !isfinite(x[1]) || !isfinite(x[2]))
@@ -656,7 +659,7 @@ __device__ inline uint32_t iso_locate(const SceneDev &S, const double x[3], int 
     for (int m = 0; m < budget; ++m) {
         iso_cell(S, c, k);
         const double y[3] = {x[0] - k.o[0], x[1] - k.o[1], x[2] - k.o[2]};
-        const bool warm = WARM && m == 0 && iso_refine(k, S.iso_scale, y, at, off);
+        const bool warm = WARM && m == 0 && iso_refine(k, S.iso_scale, y, at);
         if (!warm && !iso_local(k, S.iso_scale, y, at))
             break;
         int d[3];
@@ -873,8 +876,9 @@ __device__ inline uint32_t iso_moved(const SceneDev &S, const double x[3], const
         at.r[a] += (double)d;
         far = fmaxf(far, fabsf(d));
     }
+    at.off += far;
     IsoCell k;
-    return iso_locate<true>(S, x, nc, k, at, kIsoWalk, far + kIsoNear);
+    return iso_locate<true>(S, x, nc, k, at, kIsoWalk);
 }
 
 // --------------------------------------------------------- constitutive --
