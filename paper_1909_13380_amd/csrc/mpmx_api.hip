@@ -807,7 +807,8 @@ uint64_t layout_key(const Batch &b)
 // the stress-side and the G2P-side kernels separately (each keeps its
 // fastest repeat), and each kernel keeps its own fastest pair.  Pairs within
 // kTuneBand plus kTuneSlackMs of the fastest count as ties (the slack covers
-// the timing jitter of short kernels), and ties go to the first pair in a
+// the timing jitter of short kernels, and that the same shape of a 20 us
+// kernel takes 19.5 or 21.8 us by where a context's memory lies), and ties go to the first pair in a
 // fixed preference order (16 workgroups per CU, then 32, 8 and 64; larger
 // workgroups first), so that timing noise between nearly equal shapes does
 // not change the choice from one run to the next.
@@ -816,7 +817,7 @@ constexpr int kTuneDensity[] = {8, 16, 32, 64};
 constexpr int kNumTuneDensity = 4;
 constexpr int kTuneSteps = kTuneReps * kNumItemThreadChoices * kNumTuneDensity;
 constexpr float kTuneBand = 0.01f;
-constexpr float kTuneSlackMs = 0.002f;
+constexpr float kTuneSlackMs = 0.003f;
 static_assert(kTuneSteps + 1 <= MPMX_TUNE_MIN_STEPS, "tuning must fit in the calls it runs on");
 
 int tune(mpmx_ctx *ctx, Batch &b, LaunchCfg &best)
