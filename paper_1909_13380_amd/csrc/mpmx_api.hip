@@ -725,13 +725,14 @@ int enqueue_step(mpmx_ctx *ctx, Batch &b, const LaunchCfg &cfg, bool first, bool
 // body that spreads over more of them than the launch has workgroups leaves
 // it, and the call's remaining steps run in launches of the wide shape (128
 // threads, kWidePerCu workgroups per compute unit), which are queued behind it
-// and return at once (2 us) where it was not left.  Per step, over the whole
-// call, in separate kernels, with the one shape only, and with both (us):
-// 85184 particles that spread from 216 to 729 items 30.0, 39.5, 29.3, to 2744
-// items 46.0, 69.8, 49.0; 10648 particles to 2924 items 38.0, 57.7, 40.6 (GIMP
-// 58.8, 86.9, 55.3); 12167 particles to 3114 items with a reorder every other step
-// 62.5, 94, 73.  The wide shape at 2, 3, 4 and 6 per compute unit: 44.3, 40.6,
-// 41.5, 42.1 (10648 particles).
+// and return at once (4 to 5 us each, a call of up to 128 steps has one) where
+// it was not left.  Per step, over the whole call, in separate kernels, with
+// the one shape only, and with both (us): 85184 particles that spread from 216
+// to 729 items 30.0, 39.5, 29.3, to 2744 items 46.0, 69.8, 49.0; 10648
+// particles to 2924 items 38.0, 57.7, 40.6 (GIMP 58.8, 86.9, 55.3); 12167
+// particles to 3114 items with a reorder every other step 62.5, 94, 73.  The
+// wide shape at 2, 3, 4 and 6 per compute unit: 44.3, 40.6, 41.5, 42.1 (10648
+// particles).
 //
 // A launch costs about 25 us beyond its steps (its workgroups start, meet and
 // end), so a call needs some of them.  Whole calls of n steps in separate
@@ -808,10 +809,10 @@ uint64_t layout_key(const Batch &b)
 // fastest repeat), and each kernel keeps its own fastest pair.  Pairs within
 // kTuneBand plus kTuneSlackMs of the fastest count as ties (the slack covers
 // the timing jitter of short kernels, and that the same shape of a 20 us
-// kernel takes 19.5 or 21.8 us by where a context's memory lies), and ties go to the first pair in a
-// fixed preference order (16 workgroups per CU, then 32, 8 and 64; larger
-// workgroups first), so that timing noise between nearly equal shapes does
-// not change the choice from one run to the next.
+// kernel takes 19.5 or 21.8 us by where a context's memory lies), and ties go
+// to the first pair in a fixed preference order (16 workgroups per CU, then 32,
+// 8 and 64; larger workgroups first), so that timing noise between nearly equal
+// shapes does not change the choice from one run to the next.
 constexpr int kTuneReps = 3;
 constexpr int kTuneDensity[] = {8, 16, 32, 64};
 constexpr int kNumTuneDensity = 4;

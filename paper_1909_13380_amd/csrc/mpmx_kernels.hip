@@ -599,10 +599,10 @@ __device__ inline float iso_bend(const IsoCell &k)
     return 2.0f * m;
 }
 
-// The place of the point o + y from a guess and a step matrix: a step leaves at most bend (relative to dx/dr) off +
-// kIsoRound of itself.  The matrix is evaluated again (the price of one to two
-// steps) where the next two steps would not end the iteration.  False if it
-// broke down or did not converge.
+// The place of the point o + y from a guess and a step matrix: a step leaves
+// at most bend (relative to dx/dr) off + kIsoRound of itself.  The matrix is
+// evaluated again (the price of one to two steps) where the next two steps
+// would not end the iteration.  False if it broke down or did not converge.
 __device__ inline bool iso_refine(const IsoCell &k, float s, const double y[3], IsoAt &at)
 {
     float inv = 0.0f;
@@ -1372,10 +1372,10 @@ __device__ inline void store_rows(T *out, const T *lds, const uint32_t *pid, int
 // place of a copy of their own.  One workgroup takes kReadParticles consecutive
 // particles (a full brick's), loads the fields asked for at once (ALL: every
 // one, with no branch between the loads) and stores them one by one through
-// LDS.  Storing each particle's words from its own lane left
-// 8-byte pieces of cache lines that two XCDs' L2s completed in part: 25.2M
-// particles 3229 -> 814 us, 2.1M 174 -> 71 us (staging all fields before one
-// barrier holds 56 KB per workgroup and took 1560 and 113 us).
+// LDS.  Storing each particle's words from its own lane left 8-byte pieces of
+// cache lines that two XCDs' L2s completed in part: 25.2M particles 3229 ->
+// 814 us, 2.1M 174 -> 71 us (staging all fields before one barrier holds 56
+// KB per workgroup and took 1560 and 113 us).
 template <typename R, bool ALL>
 __global__ void __launch_bounds__(kReadThreads)
     k_read_out(const SceneDev *Sd, double *x, double *v, double *sig, double *vol, int32_t *cell, uint32_t *ctl)
@@ -3606,9 +3606,9 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 // ------------------------------------------------ many steps, one launch --
 // k_steps runs the remaining steps of a small USF batch in one launch: a
 // workgroup per item (the host's guess of how many it takes), each keeping its
-// items and their particles from step to step.  The two stages of a step are separated by a grid
-// barrier in place of the kernel boundaries, and the step control and the
-// items' start are paid once.  Between workgroups only the node buffers are
+// items and their particles from step to step.  The two stages of a step are
+// separated by a grid barrier in place of the kernel boundaries, and the step
+// control and the items' start are paid once.  Between workgroups only the node buffers are
 // shared: they are written with agent-scope atomics (adds, and the zeroing)
 // and read with agent-scope atomic loads, so the barrier needs no cache
 // write-back or invalidation: every wavefront waits until its own accesses
@@ -3640,9 +3640,10 @@ __global__ void __launch_bounds__(T) k_g2p_p2g(BatchDev B)
 // A step is bound by the chain of latencies of one item's two stages (about
 // 5 us each) and two barriers.  512 threads, one particle each, keep that
 // chain shortest (no loop over particles); with more items than workgroups the
-// shape of 128 threads and several workgroups per compute unit wins.  Measured per step against the
-// separate kernels: 1000 particles 18.9 -> 14.6 us (GIMP 29.1 -> 20.5, FP64
-// 18.9 -> 16.7, isoparametric 25.1 -> 20.0), 51200 particles 22.0 -> 16.8 us.
+// shape of 128 threads and several workgroups per compute unit wins.  Measured
+// per step against the separate kernels: 1000 particles 18.9 -> 14.6 us (GIMP
+// 29.1 -> 20.5, FP64 18.9 -> 16.7, isoparametric 25.1 -> 20.0), 51200 particles
+// 22.0 -> 16.8 us.
 
 constexpr uint64_t kStartTicks = 10000ull;       // 100 us of the 100 MHz wall clock
 constexpr uint64_t kStepTicks = 1000000000ull;   // 10 s: bound of a wait for running workgroups, which end far earlier
