@@ -640,3 +640,31 @@ def test_reading_one_field_reads_that_field(ctx, mp):
     print(f"[read-one] vol {t[0] * 1e6:.1f} us, everything {t[1] * 1e6:.1f} us", flush=True)
     assert t[0] < 0.38 * t[1], t
     s.destroy()
+
+
+def test_bodies_that_spread_in_two_contexts_at_once(mp):
+    """Two contexts whose launches both outgrow their workgroups and go on in
+    the wide shape, each with whatever part of the device the other leaves."""
+    import threading
+    scs = [_spreading(108), _spreading(109)]
+    refs = [oracle.run(sc, 105) for sc in scs]
+    out = [None, None]
+
+    def work(i):
+        c = mp.Context(0)
+        s = c.create_scene(scs[i], precision=mp.FP64)
+        for n in (60, 45):
+            s.step(n)
+        out[i] = (s.read(), s.stats())
+        s.destroy()
+        c.close()
+
+    th = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    for i in range(2):
+        got, st = out[i]
+        assert st["error_bits"] == 0 and st["steps_done"] == 105 and st["n_items"] > 1500, st
+        check(f"spread-threads/{i}", got, refs[i], scs[i]["x"], BARS["fp64"])
